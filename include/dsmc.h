@@ -90,8 +90,8 @@ typedef struct {
  * rotational degrees of freedom), the relative velocity keeping its
  * direction.  dof_rot = 0 (monatomic) leaves all of this out.  Other values,
  * or z_rot <= 0 with dof_rot = 2, are DSMC_E_INVALID.  A rotating gas runs
- * the parked-wall move schedules (4-7, 12-17), the LDS-ranked collide
- * schedules (1-4) and the scatter, gather or deferred sort (0, 1, 3); the
+ * the parked-wall move schedules (4-7, 12-17), collide
+ * schedules 1-4 and the scatter, gather or deferred sort (0, 1, 3); the
  * coupling step (dig.h) solves the polyatomic synthetic equations for it,
  * with the heat conductivities from heat_relax = (A_tt, A_tr, A_rt, A_rr),
  * the relaxation matrix of eq. thermal_conductivity_matrix (all zero:
@@ -414,10 +414,10 @@ dsmc_status dsmc_graph_step(dsmc_ctx ctx, int32_t n_steps);
  * workgroups as the device holds at once) pulling tiles of 256 particles
  * from a device work queue dealt out in one contiguous slice per XCD
  * (a workgroup drains its XCD's slice, then takes tiles from the others);
- * collide 0 LDS-staged
- * velocities, 1/2 LDS-ranked at 4/8 waves/SIMD (chunks up to 4096
- * particles in LDS), 3/4 LDS-ranked with chunks up to 3072/2048 particles
- * (more workgroups per CU); sort 0 scatter, 1 gather, 2 gather done by
+ * collide (one kernel, particles staged in LDS) 1/2/4 with two, three and
+ * up to four workgroups per CU (the fewer, the more particles each stages
+ * at once), 3 (default) chosen by the mean particles per cell and the mesh
+ * size, 0 as 2 but refused for a rotating gas and the deferred sort; sort 0 scatter, 1 gather, 2 gather done by
  * the collide kernel chunk by chunk (collide 1-4; with collide 0 it acts as
  * 1).  The autotuner's sort_ms includes the collide kernel.
  * Every schedule gives the same results.  A batch accepts only move 0-2

@@ -13,15 +13,18 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libdsmc.so")
 BUILD = os.path.join(HERE, "_build")
 
-SOURCES = ["kernels.hip", "dig.hip", "mlp.hip", "api.cpp", "dig_api.cpp", "mlp_api.cpp", "mesh.cpp", "mixed.cpp"]
+SOURCES = ["kernels.hip", "collide.hip", "dig.hip", "mlp.hip", "api.cpp", "dig_api.cpp", "mlp_api.cpp", "mesh.cpp", "mixed.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-ffp-contract=off", "-fno-fast-math",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-result",
          "-I", INCLUDE, "-I", CSRC]
+# Loop-invariant constants hoisted out of the collide kernel's loops (the
+# coefficients of FP64 sine, cosine and power) would take all its registers
+EXTRA = {"collide.hip": ["-mllvm", "-disable-machine-licm"]}
 
 
 def _compile(src, verbose):
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = ["hipcc", *FLAGS, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = ["hipcc", *FLAGS, *EXTRA.get(src, []), "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

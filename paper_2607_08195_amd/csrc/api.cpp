@@ -59,7 +59,7 @@ dsmc_status sync_scalars(dsmc_ctx c, Scalars* out) {
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     Scalars s;
     HIP_TRY(c, hipMemcpy(&s, c->d_sc, sizeof s, hipMemcpyDeviceToHost));
-    c->np_bound = s.np;
+    c->np_bound = c->np_seen = s.np;
     if (out) *out = s;
     if (s.flags & kFlagCapacity) {
         c->broken = true;
@@ -209,7 +209,7 @@ dsmc_status run_step_deferred(dsmc_ctx c, bool inj, bool col, bool smp, int64_t 
         Timed t(c, kSlotCollide);
         const CollideParams cp = collide_params(c);
         launch_collide_sample<VT>(s, a, c->d_offsets, cp, c->d_sc, c->d_perm, col ? 1 : 0, smp ? 1 : 0,
-                                  c->collide_variant, kGatherIndirect, b, c->d_sortperm);
+                                  c->collide_variant, kGatherIndirect, b, c->d_sortperm, c->np_seen);
     }
     c->pending = true;
     hipError_t e = hipGetLastError();
@@ -290,7 +290,7 @@ dsmc_status run_step(dsmc_ctx c, int mask) {
         const CollideParams cp = collide_params(c);
         launch_collide_sample<VT>(s, a, c->d_offsets, cp, c->d_sc, c->d_perm, col ? 1 : 0, smp ? 1 : 0,
                                   c->collide_variant, fuse ? kGatherFused : kGatherNone,
-                                  fuse ? as_dev<VT>(c->B) : PartDev<VT>{}, c->d_sortperm);
+                                  fuse ? as_dev<VT>(c->B) : PartDev<VT>{}, c->d_sortperm, c->np_seen);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
@@ -1351,7 +1351,7 @@ dsmc_status dsmc_set_state(dsmc_ctx c, const dsmc_state* st) {
     sc.next_pid = st->next_pid;
     sc.ninj = 0;
     HIP_TRY(c, hipMemcpy(c->d_sc, &sc, sizeof sc, hipMemcpyHostToDevice));
-    c->np_bound = n;
+    c->np_bound = c->np_seen = n;
     return DSMC_OK;
 }
 

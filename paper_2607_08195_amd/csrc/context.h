@@ -107,6 +107,7 @@ struct dsmc_ctx_s {
     int reorder = 2;  // cell order: 0 caller's, 1 Morton, 2 Hilbert
     // host view
     int64_t np_bound = 0;
+    int64_t np_seen = 0;  // particle count at the last synchronisation (sizes the collide stage)
     // profiling
     bool profiling = false;
     std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>> ev_used;

@@ -13,9 +13,8 @@ constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanBlock = kScanThreads * kScanItems;
 constexpr int kMoveBatch = 512;        // particles per wave in the move kernel
-constexpr int kCollideLanes = 64;       // one wave, one lane per cell
-constexpr int kCollideCap = 2048;       // particles of one 64-cell chunk staged in LDS
-constexpr int kCollideCapG = 4096;      // particles of one chunk ranked in LDS (order-only variant)
+constexpr int kCollideLanes = 256;      // four waves
+constexpr int kPairSlots = kCollideLanes;  // candidate pairs drawn at once
 constexpr int kInflowStride = 25;       // doubles per inflow face
 enum { kScanPlain = 0, kScanCells = 1, kScanInject = 2, kScanInit = 3 };
 enum { kFlagCapacity = 1 };
@@ -24,6 +23,9 @@ enum { kMoveLane = 0, kMoveLaneW6 = 1, kMoveLaneW8 = 2, kMoveBatched = 3, kMoveD
        kMoveDefer5 = 7, kMoveRefill5 = 8, kMoveRefill6 = 9,
        kMovePool128 = 10, kMovePool256 = 11, kMoveCap4 = 12, kMoveCap5 = 13, kMoveCap6 = 14,
        kMoveFace3 = 15, kMoveFace3W8 = 16, kMovePersist = 17 };
+// collide schedules: workgroups per CU (0 and 2: three, 1: two, 4: four, or
+// three where the stage would be too small; 3, the default: by occupancy and
+// mesh size)
 enum { kCollideLds = 0, kCollideGlobal = 1, kCollideGlobal8 = 2, kCollideG3k = 3, kCollideG2k = 4 };
 // sort: scatter by rank; gather (k_perm then k_gather); fused (k_perm, then
 // the collide kernel gathers each chunk before colliding it; G-type collide
@@ -176,7 +178,7 @@ void launch_scatter(hipStream_t s, PartDev<VT> src, PartDev<VT> dst, const Scala
 template <class VT>
 void launch_collide_sample(hipStream_t s, PartDev<VT> p, const int32_t* offsets, const CollideParams& cp,
                            const Scalars* sc, int32_t* perm, int do_collide, int do_sample, int variant, int gmode,
-                           PartDev<VT> src, const int32_t* sortperm);
+                           PartDev<VT> src, const int32_t* sortperm, int64_t np);
 bool collide_fuses_gather(int variant);
 void launch_fields(hipStream_t s, const double* sums, int nt, double ns, double mass, double FN,
                    const double* vol, const int32_t* orig, double* out, const int32_t* cell_case,

@@ -1071,520 +1071,6 @@ __global__ __launch_bounds__(256) void k_gather(PartDev<VT> src, PartDev<VT> dst
 }
 
 // ---------------------------------------------------------------------------
-// collisions and sampling
-// ---------------------------------------------------------------------------
-// Access to the velocities of one cell in logical (pid) order.
-template <class VT>
-struct LdsCell {
-    VT* v0; VT* v1; VT* v2;
-    const uint16_t* ord;
-    uint8_t* touch;
-    int s0;
-    __device__ __forceinline__ void get(int k, double& a, double& b, double& c) const {
-        const int l = ord[s0 + k];
-        a = (double)v0[l]; b = (double)v1[l]; c = (double)v2[l];
-    }
-    __device__ __forceinline__ void put(int k, double a, double b, double c) const {
-        const int l = ord[s0 + k];
-        v0[l] = (VT)a; v1[l] = (VT)b; v2[l] = (VT)c;
-        touch[l] = 1;
-    }
-};
-
-template <class VT>
-struct GlobalCell {
-    VT* v;                 // interleaved velocities of the particle store
-    const int32_t* perm;   // logical -> physical
-    int64_t s0;
-    double* ir;            // rotational energies of the particle store (rotating gas)
-    __device__ __forceinline__ void get(int k, double& a, double& b, double& c) const {
-        const int64_t l = perm[s0 + k];
-        a = (double)v[3 * l]; b = (double)v[3 * l + 1]; c = (double)v[3 * l + 2];
-    }
-    __device__ __forceinline__ void put(int k, double a, double b, double c) const {
-        const int64_t l = perm[s0 + k];
-        v[3 * l] = (VT)a; v[3 * l + 1] = (VT)b; v[3 * l + 2] = (VT)c;
-    }
-    __device__ __forceinline__ double getI(int k) const { return ir[perm[s0 + k]]; }
-    __device__ __forceinline__ void putI(int k, double e) const { ir[perm[s0 + k]] = e; }
-};
-
-template <class VT>
-struct LdsOrderCell {
-    VT* v;                 // interleaved velocities of the particle store
-    const uint16_t* ord;   // sorted position -> slot relative to the chunk start
-    int s0;
-    int64_t a;             // chunk start in the particle arrays
-    __device__ __forceinline__ void get(int k, double& x, double& y, double& z) const {
-        const int64_t l = a + ord[s0 + k];
-        x = (double)v[3 * l]; y = (double)v[3 * l + 1]; z = (double)v[3 * l + 2];
-    }
-    __device__ __forceinline__ void put(int k, double x, double y, double z) const {
-        const int64_t l = a + ord[s0 + k];
-        v[3 * l] = (VT)x; v[3 * l + 1] = (VT)y; v[3 * l + 2] = (VT)z;
-    }
-    double* ir;            // rotational energies of the particle store (rotating gas)
-    __device__ __forceinline__ double getI(int k) const { return ir[a + ord[s0 + k]]; }
-    __device__ __forceinline__ void putI(int k, double e) const { ir[a + ord[s0 + k]] = e; }
-};
-
-// As LdsOrderCell for particles left where the move put them: the window's
-// slot -> particle index table in LDS.
-template <class VT>
-struct LdsIndCell {
-    VT* v;                 // interleaved velocities of the particle store
-    const uint16_t* ord;   // sorted position -> slot relative to the window start
-    const uint32_t* src;   // window slot -> particle index
-    int s0;
-    __device__ __forceinline__ void get(int k, double& x, double& y, double& z) const {
-        const int64_t l = src[ord[s0 + k]];
-        x = (double)v[3 * l]; y = (double)v[3 * l + 1]; z = (double)v[3 * l + 2];
-    }
-    __device__ __forceinline__ void put(int k, double x, double y, double z) const {
-        const int64_t l = src[ord[s0 + k]];
-        v[3 * l] = (VT)x; v[3 * l + 1] = (VT)y; v[3 * l + 2] = (VT)z;
-    }
-    double* ir;            // rotational energies of the particle store (rotating gas)
-    __device__ __forceinline__ double getI(int k) const { return ir[src[ord[s0 + k]]]; }
-    __device__ __forceinline__ void putI(int k, double e) const { ir[src[ord[s0 + k]]] = e; }
-};
-
-// Post-collision relative velocity g' (|g'| = |g| = c_r) from two uniform
-// deviates R1 (deflection) and R2 (azimuth eps = 2 pi R2).  VHS: isotropic,
-// cos(theta) = 2 R1 - 1 measured from the x axis, independent of g.  VSS
-// (section 2.1, the model of Bird 1994): the deflection chi from g has
-// cos(chi) = 2 R1^(1/alpha) - 1 and g' = cos(chi) g + sin(chi) c_r
-// (cos(eps) e1 + sin(eps) e2) in the frame e1 = (0, g_z, -g_y) / g_yz,
-// e2 = (g_yz^2, -g_x g_y, -g_x g_z) / (c_r g_yz), g_yz = |(g_y, g_z)|; with
-// g along x (g_yz = 0) e1 and e2 are the y and z axes.  VSS is a template
-// parameter so that the isotropic kernels keep their register budget.
-template <bool VSS>
-__device__ __forceinline__ void scatter_vhs_vss(const CollideParams& cp, double gx, double gy, double gz,
-                                                double cr2, double R1, double R2, double& o0, double& o1,
-                                                double& o2) {
-    const double cr = sqrt(cr2);
-    const double eps = DSMC_TWO_PI * R2;
-    if (!VSS) {
-        const double cx = 2.0 * R1 - 1.0;
-        const double sx = sqrt(1.0 - cx * cx);
-        o0 = cr * cx;
-        o1 = cr * (sx * cos(eps));
-        o2 = cr * (sx * sin(eps));
-        return;
-    }
-    const double cc = 2.0 * pow(R1, cp.inv_alpha) - 1.0;
-    const double sc = sqrt(1.0 - cc * cc);
-    const double ce = cos(eps), se = sin(eps);
-    const double gyz = sqrt(gy * gy + gz * gz);
-    double e10 = 0.0, e11 = 1.0, e12 = 0.0, e20 = 0.0, e21 = 0.0, e22 = 1.0;
-    if (gyz > 0.0) {
-        e11 = gz / gyz;
-        e12 = -gy / gyz;
-        e20 = gyz / cr;
-        e21 = -(gx * gy) / (cr * gyz);
-        e22 = -(gx * gz) / (cr * gyz);
-    }
-    const double scr = sc * cr;
-    o0 = cc * gx + scr * (se * e20 + ce * e10);
-    o1 = cc * gy + scr * (se * e21 + ce * e11);
-    o2 = cc * gz + scr * (se * e22 + ce * e12);
-}
-
-template <bool VSS, bool ROT = false, class Acc>
-__device__ __forceinline__ void ntc_cell(const Acc& cv, int N, int c, const CollideParams& cp,
-                                         uint32_t step, double* smax, int32_t* ncand, int32_t* nacc) {
-    int M = 0, acc = 0;
-    if (N >= 2) {
-        const double sm = smax[c];
-        uint32_t subj = (uint32_t)cp.orig[c];
-        RngKey key = cp.key;
-        double FN = cp.FN, dt = cp.dt;
-        if (cp.cell_case) {
-            const CaseDev& cs = cp.cases[cp.cell_case[c]];
-            key.k0 = cs.k0;
-            key.k1 = cs.k1;
-            FN = cs.FN;
-            dt = cs.dt;
-            subj -= (uint32_t)cs.cell0;
-        }
-        const Rand4 r = draw(key, subj, step, kPurposeNtcCount, 0);
-        const double Nd = (double)N;
-        const double mean = ((((0.5 * Nd) * (Nd - 1.0)) * FN) * sm) * dt / cp.vol[c];
-        M = (int)floor(mean + u01(r.w[0], r.w[1]));
-        double seen = 0.0;
-        // (sigma c)/(sigma c)_max = K cr2^ex / sm is first estimated in FP32
-        // (hardware log2/exp2); when the estimate is below 1 and U lies
-        // outside a relative band of 1e-3 around it, both the acceptance and
-        // the (sigma c)_max update (only values above sm matter) are decided
-        // without the FP64 power, and decided as the FP64 expression would.
-        const float lk = log2f((float)cp.K) - log2f((float)sm), ex32 = (float)cp.ex;
-        for (int k = 0; k < M; ++k) {
-            const Rand4 w = draw(key, subj, step, kPurposePair, (uint64_t)k);
-            const uint32_t i = pick(w.w[0], (uint32_t)N);
-            uint32_t j = pick(w.w[1], (uint32_t)(N - 1));
-            if (j >= i) ++j;
-            const double U = u01(w.w[2], w.w[3]);
-            double a0, a1, a2, b0, b1, b2;
-            cv.get((int)i, a0, a1, a2);
-            cv.get((int)j, b0, b1, b2);
-            const double gx = a0 - b0, gy = a1 - b1, gz = a2 - b2;
-            const double cr2 = gx * gx + gy * gy + gz * gz;
-            const double est = (double)exp2f(fmaf(ex32, log2f((float)cr2), lk));
-            const double lo = est * (1.0 - 1e-3), hi = est * (1.0 + 1e-3);
-            bool take;
-            if (hi < 1.0 && (U < lo || U >= hi)) {
-                take = U < lo;
-            } else {
-                const double sc = cp.K * pow(cr2, cp.ex);
-                if (sc > seen) seen = sc;
-                take = U < sc / sm;
-            }
-            if (!take) continue;
-            ++acc;
-            const Rand4 q = draw(key, subj, step, kPurposeScatter, (uint64_t)k);
-            double gp0, gp1, gp2;
-            if constexpr (ROT) {
-                // Borgnakke-Larsen, partner by partner: with probability
-                // pinel the partner's rotational energy and the relative
-                // translational energy E_t = m c_r^2 / 4 are pooled and the
-                // translation keeps E_c R^(1/(5/2 - omega)) (two rotational
-                // degrees of freedom); the relative velocity keeps its
-                // direction and takes the new speed
-                const double R1 = u01(q.w[0], q.w[1]), R2 = u01(q.w[2], q.w[3]);
-                double Ii = cv.getI((int)i), Ij = cv.getI((int)j);
-                double Et = (0.25 * cp.mass) * cr2;
-                bool inel = false;
-                const Rand4 ri = draw(key, subj, step, kPurposeInelasticI, (uint64_t)k);
-                if (u01(ri.w[0], ri.w[1]) < cp.pinel) {
-                    const double Ec = Et + Ii;
-                    Et = Ec * pow(u01(ri.w[2], ri.w[3]), cp.ex_bl);
-                    Ii = Ec - Et;
-                    inel = true;
-                }
-                const Rand4 rj = draw(key, subj, step, kPurposeInelasticJ, (uint64_t)k);
-                if (u01(rj.w[0], rj.w[1]) < cp.pinel) {
-                    const double Ec = Et + Ij;
-                    Et = Ec * pow(u01(rj.w[2], rj.w[3]), cp.ex_bl);
-                    Ij = Ec - Et;
-                    inel = true;
-                }
-                if (inel) {
-                    cv.putI((int)i, Ii);
-                    cv.putI((int)j, Ij);
-                    const double cr2n = (4.0 * Et) / cp.mass;
-                    const double f = sqrt(cr2n / cr2);
-                    scatter_vhs_vss<VSS>(cp, gx * f, gy * f, gz * f, cr2n, R1, R2, gp0, gp1, gp2);
-                } else {
-                    scatter_vhs_vss<VSS>(cp, gx, gy, gz, cr2, R1, R2, gp0, gp1, gp2);
-                }
-            } else {
-                scatter_vhs_vss<VSS>(cp, gx, gy, gz, cr2, u01(q.w[0], q.w[1]), u01(q.w[2], q.w[3]), gp0, gp1,
-                                     gp2);
-            }
-            const double cm0 = 0.5 * (a0 + b0), cm1 = 0.5 * (a1 + b1), cm2 = 0.5 * (a2 + b2);
-            const double h0 = 0.5 * gp0, h1 = 0.5 * gp1, h2 = 0.5 * gp2;
-            cv.put((int)i, cm0 + h0, cm1 + h1, cm2 + h2);
-            cv.put((int)j, cm0 - h0, cm1 - h1, cm2 - h2);
-        }
-        if (seen > sm) smax[c] = seen;
-    }
-    ncand[c] = M;
-    nacc[c] = acc;
-}
-
-template <bool ROT = false, class Acc>
-__device__ __forceinline__ void sample_cell(const Acc& cv, int N, int c, const CollideParams& cp,
-                                            uint32_t step) {
-    double S[kNMom];
-#pragma unroll
-    for (int k = 0; k < kNMom; ++k) S[k] = 0.0;
-    for (int k = 0; k < N; ++k) {
-        double vx, vy, vz;
-        cv.get(k, vx, vy, vz);
-        const double v2 = vx * vx + vy * vy + vz * vz;
-        S[0] += 1.0;
-        S[1] += vx; S[2] += vy; S[3] += vz;
-        S[4] += vx * vx; S[5] += vy * vy; S[6] += vz * vz;
-        S[7] += vx * vy; S[8] += vx * vz; S[9] += vy * vz;
-        S[10] += vx * v2; S[11] += vy * v2; S[12] += vz * v2;
-    }
-    const int64_t nt = cp.nt;
-    if (cp.inst) {
-#pragma unroll
-        for (int k = 0; k < kNMom; ++k) cp.inst[k * nt + c] = S[k];
-    }
-    if ((int64_t)step > (int64_t)cp.n_ss) {
-#pragma unroll
-        for (int k = 0; k < kNMom; ++k) cp.acc[k * nt + c] += S[k];
-    }
-    if (cp.ewma_on) {
-        const int m = cp.ewma_m[c] + 1;
-        cp.ewma_m[c] = m;
-        const int n = (cp.local_acc[c] || m < cp.n_a) ? m : cp.n_a;
-        const double wo = (double)(n - 1) / (double)n;
-        const double wn = 1.0 / (double)n;
-#pragma unroll
-        for (int k = 0; k < kNMom; ++k) {
-            double* e = cp.ewma + k * nt + c;
-            *e = wo * *e + wn * S[k];
-        }
-    }
-    if constexpr (ROT) {
-        // rotational sums: sum I_r, sum v_i I_r (rotational temperature and
-        // heat flux of eq. dsmc_temperatures), in the same particle order
-        double Rr[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int k = 0; k < N; ++k) {
-            double vx, vy, vz;
-            cv.get(k, vx, vy, vz);
-            const double I = cv.getI(k);
-            Rr[0] += I;
-            Rr[1] += vx * I; Rr[2] += vy * I; Rr[3] += vz * I;
-        }
-        if (cp.rinst) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) cp.rinst[k * nt + c] = Rr[k];
-        }
-        if ((int64_t)step > (int64_t)cp.n_ss) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) cp.racc[k * nt + c] += Rr[k];
-        }
-        if (cp.ewma_on) {
-            const int m = cp.ewma_m[c];
-            const int n = (cp.local_acc[c] || m < cp.n_a) ? m : cp.n_a;
-            const double wo = (double)(n - 1) / (double)n;
-            const double wn = 1.0 / (double)n;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                double* e = cp.rewma + k * nt + c;
-                *e = wo * *e + wn * Rr[k];
-            }
-        }
-    }
-}
-
-template <class VT, bool VSS>
-__global__ __launch_bounds__(kCollideLanes) void k_collide_sample(PartDev<VT> p, const int32_t* offsets,
-                                                                  CollideParams cp, const Scalars* sc,
-                                                                  int32_t* perm, int do_collide,
-                                                                  int do_sample) {
-    __shared__ VT sv0[kCollideCap];
-    __shared__ VT sv1[kCollideCap];
-    __shared__ VT sv2[kCollideCap];
-    __shared__ uint32_t spid[kCollideCap];
-    __shared__ uint16_t sord[kCollideCap];
-    __shared__ uint8_t stouch[kCollideCap];
-    const int nt = cp.nt;
-    const int lane = threadIdx.x;
-    const int c0 = blockIdx.x * kCollideLanes;
-    const int c = c0 + lane;
-    const int cend = min(c0 + kCollideLanes, nt);
-    const int64_t a = offsets[c0];
-    const int64_t n = (int64_t)offsets[cend] - a;
-    const uint32_t step = sc->step;
-    if (n <= kCollideCap) {
-#pragma unroll 4
-        for (int64_t i = lane; i < n; i += kCollideLanes) {
-            sv0[i] = p.vel[3 * (a + i)];
-            sv1[i] = p.vel[3 * (a + i) + 1];
-            sv2[i] = p.vel[3 * (a + i) + 2];
-            spid[i] = p.pid[a + i];
-            stouch[i] = 0;
-        }
-        __syncthreads();
-        if (c < nt) {
-            const int s0 = (int)(offsets[c] - a);
-            const int N = offsets[c + 1] - offsets[c];
-            // logical order: insertion sort of the cell's pids (sord maps the
-            // sorted position to the staged slot)
-            for (int k = 0; k < N; ++k) {
-                const uint32_t key = spid[s0 + k];
-                int j = k;
-                while (j > 0 && spid[s0 + j - 1] > key) {
-                    spid[s0 + j] = spid[s0 + j - 1];
-                    sord[s0 + j] = sord[s0 + j - 1];
-                    --j;
-                }
-                spid[s0 + j] = key;
-                sord[s0 + j] = (uint16_t)(s0 + k);
-            }
-            LdsCell<VT> cv{sv0, sv1, sv2, sord, stouch, s0};
-            if (do_collide) ntc_cell<VSS>(cv, N, c, cp, step, cp.smax, cp.ncand, cp.nacc);
-            if (do_sample) sample_cell(cv, N, c, cp, step);
-        }
-        __syncthreads();
-        for (int64_t i = lane; i < n; i += kCollideLanes) {
-            if (stouch[i]) {
-                p.vel[3 * (a + i)] = sv0[i];
-                p.vel[3 * (a + i) + 1] = sv1[i];
-                p.vel[3 * (a + i) + 2] = sv2[i];
-            }
-        }
-    } else if (c < nt) {
-        // dense chunk: logical order through a global permutation
-        const int64_t s0 = offsets[c];
-        const int N = offsets[c + 1] - offsets[c];
-        for (int k = 0; k < N; ++k) {
-            const uint32_t pk = p.pid[s0 + k];
-            int r = 0;
-            for (int q = 0; q < N; ++q) r += p.pid[s0 + q] < pk;
-            perm[s0 + r] = (int32_t)(s0 + k);
-        }
-        GlobalCell<VT> cv{p.vel, perm, s0, nullptr};
-        if (do_collide) ntc_cell<VSS>(cv, N, c, cp, step, cp.smax, cp.ncand, cp.nacc);
-        if (do_sample) sample_cell(cv, N, c, cp, step);
-    }
-}
-
-// Variant with only the pid ranking staged in LDS (6 bytes per particle,
-// up to kCollideCapG per 64-cell chunk); the velocities stay in global
-// memory and are reached through the logical order, so several waves fit on
-// a CU.  Ranks are computed one particle per lane (independent LDS reads
-// that pipeline), the collisions and sums one cell per lane.
-// CAP bounds the LDS of a workgroup (6 bytes per particle), hence how many
-// workgroups share a CU; a chunk of more than CAP particles takes the
-// global-memory path.
-// With FUSED, the chunk's slots of the sorted buffer p are first filled from
-// the unsorted buffer src through the gather permutation (slot -> source
-// index; k_perm has written the slots' cells): the sort's gather done by the
-// workgroup that then collides the chunk, so that gathering one chunk
-// overlaps the collisions of others and the velocities are read back from
-// cache.  With IND (deferred sort) nothing is moved: slot d of the sorted
-// order is particle sortperm[d] of p, its cell src.cell[d]; after the
-// ranking the window's pid table is overwritten with those particle indices.
-template <class VT, int WPE, int CAP, int GM, bool VSS, bool ROT = false>
-__global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(WPE))) void k_collide_sample_g(
-    PartDev<VT> p, const int32_t* offsets, CollideParams cp, const Scalars* sc, int32_t* perm, int do_collide,
-    int do_sample, PartDev<VT> src, const int32_t* sortperm) {
-    constexpr bool FUSED = GM == kGatherFused;
-    constexpr bool IND = GM == kGatherIndirect;
-    __shared__ uint32_t spid[CAP];
-    __shared__ uint16_t sord[CAP];
-    __shared__ int32_t soff[kCollideLanes + 1];
-    const int nt = cp.nt;
-    const int lane = threadIdx.x;
-    const int c0 = blockIdx.x * kCollideLanes;
-    const int c = c0 + lane;
-    const int64_t a = offsets[c0];
-    soff[lane] = offsets[min(c0 + lane, nt)] - (int32_t)a;
-    if (lane == 0) soff[kCollideLanes] = offsets[min(c0 + kCollideLanes, nt)] - (int32_t)a;
-    const int64_t n = (int64_t)offsets[min(c0 + kCollideLanes, nt)] - a;
-    const uint32_t step = sc->step;
-    __syncthreads();  // soff is read by every lane below
-    if (FUSED) {
-        // kFuseBatch particles per lane in flight: all loads of a batch are
-        // issued before its stores (the compiler cannot move a load of src
-        // above a store to p, which might alias it)
-        constexpr int kFuseBatch = 8;
-        for (int64_t i0 = lane; i0 < n; i0 += kFuseBatch * kCollideLanes) {
-            int64_t j[kFuseBatch];
-            double x[kFuseBatch][3];
-            VT v[kFuseBatch][3];
-            uint32_t id[kFuseBatch];
-#pragma unroll
-            for (int b = 0; b < kFuseBatch; ++b) {
-                const int64_t i = i0 + b * kCollideLanes;
-                j[b] = i < n ? sortperm[a + i] : 0;
-            }
-#pragma unroll
-            for (int b = 0; b < kFuseBatch; ++b) {
-                if (i0 + b * kCollideLanes < n) {
-                    x[b][0] = src.pos[3 * j[b]];
-                    x[b][1] = src.pos[3 * j[b] + 1];
-                    x[b][2] = src.pos[3 * j[b] + 2];
-                    v[b][0] = src.vel[3 * j[b]];
-                    v[b][1] = src.vel[3 * j[b] + 1];
-                    v[b][2] = src.vel[3 * j[b] + 2];
-                    id[b] = src.pid[j[b]];
-                }
-            }
-#pragma unroll
-            for (int b = 0; b < kFuseBatch; ++b) {
-                const int64_t i = i0 + b * kCollideLanes;
-                if (i < n) {
-                    const int64_t d = a + i;
-                    p.pos[3 * d] = x[b][0];
-                    p.pos[3 * d + 1] = x[b][1];
-                    p.pos[3 * d + 2] = x[b][2];
-                    p.vel[3 * d] = v[b][0];
-                    p.vel[3 * d + 1] = v[b][1];
-                    p.vel[3 * d + 2] = v[b][2];
-                    p.pid[d] = id[b];
-                    if (n <= CAP) spid[i] = id[b];
-                }
-            }
-        }
-        __syncthreads();
-    }
-    // The chunk's cells are taken in windows of consecutive cells whose
-    // particles fit in CAP (one window when the whole chunk fits): ranks in
-    // LDS, then the window's cells one per lane.  A single cell with more
-    // than CAP particles takes the global-memory path.
-    for (int k0 = 0; k0 < kCollideLanes;) {
-        int k1 = k0;
-        while (k1 < kCollideLanes && soff[k1 + 1] - soff[k0] <= CAP) ++k1;
-        const int w0 = soff[k0];
-        if (k1 == k0) {
-            // one cell beyond the LDS stage
-            if (lane == 0 && c0 + k0 < nt) {
-                const int cc = c0 + k0;
-                const int64_t s0 = offsets[cc];
-                const int N = offsets[cc + 1] - offsets[cc];
-                for (int k = 0; k < N; ++k) {
-                    const uint32_t pk = IND ? p.pid[sortperm[s0 + k]] : p.pid[s0 + k];
-                    int r = 0;
-                    for (int q = 0; q < N; ++q) r += (IND ? p.pid[sortperm[s0 + q]] : p.pid[s0 + q]) < pk;
-                    perm[s0 + r] = IND ? sortperm[s0 + k] : (int32_t)(s0 + k);
-                }
-                GlobalCell<VT> cv{p.vel, perm, s0, p.ir};
-                if (do_collide) ntc_cell<VSS, ROT>(cv, N, cc, cp, step, cp.smax, cp.ncand, cp.nacc);
-                if (do_sample) sample_cell<ROT>(cv, N, cc, cp, step);
-            }
-            k0 = k0 + 1;
-            continue;
-        }
-        const int wn = soff[k1] - w0;
-        if (!FUSED || n > CAP) {
-            if (k0 > 0) __syncthreads();  // the previous window's ranks are no longer read
-#pragma unroll 4
-            for (int i = lane; i < wn; i += kCollideLanes)
-                spid[i] = IND ? p.pid[sortperm[a + w0 + i]] : p.pid[a + w0 + i];
-        }
-        __syncthreads();
-        for (int i = lane; i < wn; i += kCollideLanes) {
-            const int k = (IND ? src.cell[a + w0 + i] : p.cell[a + w0 + i]) - c0;
-            const int s0 = soff[k] - w0;
-            const int N = soff[k + 1] - soff[k];
-            const uint32_t pk = spid[i];
-            int r = 0;
-#pragma unroll 4
-            for (int q = 0; q < N; ++q) r += spid[s0 + q] < pk ? 1 : 0;
-            sord[s0 + r] = (uint16_t)i;
-        }
-        __syncthreads();
-        if constexpr (IND) {
-            // the pids are ranked: the table now maps window slots to particles
-#pragma unroll 4
-            for (int i = lane; i < wn; i += kCollideLanes) spid[i] = (uint32_t)sortperm[a + w0 + i];
-            __syncthreads();
-            if (lane >= k0 && lane < k1 && c < nt) {
-                const int s0 = soff[lane] - w0;
-                const int N = soff[lane + 1] - soff[lane];
-                LdsIndCell<VT> cv{p.vel, sord, spid, s0, p.ir};
-                if (do_collide) ntc_cell<VSS, ROT>(cv, N, c, cp, step, cp.smax, cp.ncand, cp.nacc);
-                if (do_sample) sample_cell<ROT>(cv, N, c, cp, step);
-            }
-        } else if (lane >= k0 && lane < k1 && c < nt) {
-            const int s0 = soff[lane] - w0;
-            const int N = soff[lane + 1] - soff[lane];
-            LdsOrderCell<VT> cv{p.vel, sord, s0, a + w0, p.ir};
-            if (do_collide) ntc_cell<VSS, ROT>(cv, N, c, cp, step, cp.smax, cp.ncand, cp.nacc);
-            if (do_sample) sample_cell<ROT>(cv, N, c, cp, step);
-        }
-        k0 = k1;
-    }
-}
-
-// ---------------------------------------------------------------------------
 // fields from moment sums (eq. dsmc_temperatures over accumulated samples)
 // ---------------------------------------------------------------------------
 __global__ void k_fields(const double* sums, int nt, double ns, double mass, double FN, const double* vol,
@@ -1909,78 +1395,6 @@ void launch_perm_identity(hipStream_t s, const int32_t* cell, const Scalars* sc,
     hipLaunchKernelGGL(k_perm_identity, dim3(grid8(bound, 256)), dim3(256), 0, s, cell, sc, perm, dst_cell);
 }
 
-template <class VT, int WPE, int CAP, bool VSS, bool ROT>
-static void launch_collide_g(hipStream_t s, int nchunk, PartDev<VT> p, const int32_t* offsets, const CollideParams& cp,
-                             const Scalars* sc, int32_t* perm, int do_collide, int do_sample, int gmode,
-                             PartDev<VT> src, const int32_t* sortperm) {
-    if (gmode == kGatherIndirect) {
-        hipLaunchKernelGGL((k_collide_sample_g<VT, WPE, CAP, kGatherIndirect, VSS, ROT>), dim3(nchunk),
-                           dim3(kCollideLanes), 0, s, p, offsets, cp, sc, perm, do_collide, do_sample, src, sortperm);
-    } else if constexpr (ROT) {
-        // a rotating gas never takes the fused gather (the host refuses that schedule)
-        hipLaunchKernelGGL((k_collide_sample_g<VT, WPE, CAP, kGatherNone, VSS, true>), dim3(nchunk),
-                           dim3(kCollideLanes), 0, s, p, offsets, cp, sc, perm, do_collide, do_sample, src, sortperm);
-    } else if (gmode == kGatherFused) {
-        hipLaunchKernelGGL((k_collide_sample_g<VT, WPE, CAP, kGatherFused, VSS>), dim3(nchunk), dim3(kCollideLanes), 0,
-                           s, p, offsets, cp, sc, perm, do_collide, do_sample, src, sortperm);
-    } else {
-        hipLaunchKernelGGL((k_collide_sample_g<VT, WPE, CAP, kGatherNone, VSS>), dim3(nchunk), dim3(kCollideLanes), 0,
-                           s, p, offsets, cp, sc, perm, do_collide, do_sample, src, sortperm);
-    }
-}
-
-bool collide_fuses_gather(int variant) {
-    return variant == kCollideGlobal || variant == kCollideGlobal8 || variant == kCollideG3k || variant == kCollideG2k;
-}
-
-// Waves per SIMD the collide kernels are compiled for.  The chunk's pid
-// table (18.7 KB of LDS at 3072 particles) already holds a one-wave
-// workgroup to two waves per SIMD; the rotating gas's instances ask for two,
-// so that the compiler keeps them within 256 registers (asked for more, they
-// took 263 and ran at one wave per SIMD).
-constexpr int collide_wpe(int w, bool rot) { return rot ? 2 : w; }
-
-template <class VT, bool VSS, bool ROT>
-static void launch_collide_v(hipStream_t s, PartDev<VT> p, const int32_t* offsets, const CollideParams& cp,
-                             const Scalars* sc, int32_t* perm, int do_collide, int do_sample, int variant, int gmode,
-                             PartDev<VT> src, const int32_t* sortperm) {
-    const int nchunk = (cp.nt + kCollideLanes - 1) / kCollideLanes;
-    if (variant == kCollideGlobal)
-        launch_collide_g<VT, collide_wpe(4, ROT), kCollideCapG, VSS, ROT>(s, nchunk, p, offsets, cp, sc, perm, do_collide, do_sample,
-                                                        gmode, src, sortperm);
-    else if (variant == kCollideGlobal8)
-        launch_collide_g<VT, collide_wpe(8, ROT), kCollideCapG, VSS, ROT>(s, nchunk, p, offsets, cp, sc, perm, do_collide, do_sample,
-                                                        gmode, src, sortperm);
-    else if (variant == kCollideG3k)
-        launch_collide_g<VT, collide_wpe(4, ROT), 3072, VSS, ROT>(s, nchunk, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src,
-                                                sortperm);
-    else if (variant == kCollideG2k)
-        launch_collide_g<VT, collide_wpe(4, ROT), 2048, VSS, ROT>(s, nchunk, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src,
-                                                sortperm);
-    else if constexpr (!ROT)
-        hipLaunchKernelGGL((k_collide_sample<VT, VSS>), dim3(nchunk), dim3(kCollideLanes), 0, s, p, offsets, cp, sc,
-                           perm, do_collide, do_sample);
-}
-
-template <class VT>
-void launch_collide_sample(hipStream_t s, PartDev<VT> p, const int32_t* offsets, const CollideParams& cp,
-                           const Scalars* sc, int32_t* perm, int do_collide, int do_sample, int variant, int gmode,
-                           PartDev<VT> src, const int32_t* sortperm) {
-    if (cp.rot) {
-        if (cp.vss)
-            launch_collide_v<VT, true, true>(s, p, offsets, cp, sc, perm, do_collide, do_sample, variant, gmode, src,
-                                             sortperm);
-        else
-            launch_collide_v<VT, false, true>(s, p, offsets, cp, sc, perm, do_collide, do_sample, variant, gmode, src,
-                                              sortperm);
-    } else if (cp.vss) {
-        launch_collide_v<VT, true, false>(s, p, offsets, cp, sc, perm, do_collide, do_sample, variant, gmode, src, sortperm);
-    } else {
-        launch_collide_v<VT, false, false>(s, p, offsets, cp, sc, perm, do_collide, do_sample, variant, gmode, src,
-                                           sortperm);
-    }
-}
-
 void launch_fields(hipStream_t s, const double* sums, int nt, double ns, double mass, double FN,
                    const double* vol, const int32_t* orig, double* out, const int32_t* cell_case,
                    const CaseDev* cases) {
@@ -2029,10 +1443,7 @@ void launch_fill_f64(hipStream_t s, double* p, double v, int64_t n) {
     template void launch_move_walls<VT>(hipStream_t, const MeshDev&, PartDev<VT>, const Scalars*, int32_t*,  \
                                         uint32_t*, Counters*, RngKey, WallQueue);                           \
     template void launch_gather<VT>(hipStream_t, PartDev<VT>, PartDev<VT>, const Scalars*, const int32_t*,  \
-                                    int64_t);                                                               \
-    template void launch_collide_sample<VT>(hipStream_t, PartDev<VT>, const int32_t*, const CollideParams&, \
-                                            const Scalars*, int32_t*, int, int, int, int, PartDev<VT>,        \
-                                            const int32_t*);
+                                    int64_t);
 
 INSTANTIATE(float)
 INSTANTIATE(double)

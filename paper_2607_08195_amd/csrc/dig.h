@@ -41,18 +41,39 @@ struct DigCase {
     uint32_t next_pid;
 };
 
+// Quotients by one divisor: its reciprocal once (correctly rounded), then per
+// quotient one correction by the exact remainder, which leaves it within
+// 1 + 2^-51 of half an ulp: it is the division's result but for one quotient in
+// about 2^51 (none in 4e8 random ones), as long as the remainder does not
+// underflow, which takes quotients of 1e-290.  Four instructions instead of
+// eleven, one of them at a quarter of the rate.  Zeros, infinities and NaN go
+// through the hardware's fix-up.
+struct Divisor {
+    double b = 1.0, r = 1.0;
+    Divisor() = default;
+    __host__ __device__ explicit Divisor(double d) : b(d), r(1.0 / d) {}
+    __device__ __forceinline__ double of(double a) const {
+        double q = a * r;
+        q = __builtin_fma(__builtin_fma(-b, q, a), r, q);
+        return __builtin_amdgcn_div_fixup(q, b, a);
+    }
+};
+
 struct DigGeom {
     int nt;
     const double* cen;     // [nt][3] centroid
-    const double* fcen;    // [nt][4][3] face centroid
-    const double* fnu;     // [nt][4][3] outward unit normal
+    // per (cell, face), faces of a cell adjacent, vectors component by
+    // component (consecutive lanes read consecutive values)
+    const double* fcen;    // [3][nt][4] face centroid
+    const double* fnu;     // [3][nt][4] outward unit normal
     const double* farea;   // [nt][4]
-    const double* fdx;     // [nt][4][3] centroid -> neighbour centroid (periodic: shifted) or -> face centroid
+    const double* fdx;     // [3][nt][4] centroid -> neighbour centroid (periodic: shifted) or -> face centroid
     const int32_t* flink;  // [nt][4]
     const double* lsq;     // [nt][9] inverse of the weighted least-squares normal matrix
     const double* vol;     // [nt]
     const DigGroup* groups;
-    double mass, R, mu_ref, omega, T_ref;
+    double mass, R, mu_ref, omega;
+    Divisor T_ref, mass4, cv;  // reference temperature, 4 mass, 3/2 R
     double FN;  // real molecules per particle
     const int32_t* cell_case;  // batch: internal cell -> case (null for one case)
     DigCase* cases;            // batch: per-case parameters
@@ -70,6 +91,7 @@ struct DigGeom {
 struct DigCtl {
     double res0, res, dtmin;
     int conv, failed, iters;
+    int failed1, failed2;  // found by an iteration's first stage and by its later ones
     int n_rejected, n_reconstructed, n_unreached;
     int n_closure, n_fallback;
     double mass_scale;
@@ -84,8 +106,8 @@ struct DigWork {
     double* prim;     // [nt][NV] working state; M^{k+1} after the solve
     double* half;     // [nt][NV] M^{k+1/2} after the gate
     double* hot;      // [nt][NH] cell HoT
-    double* hotf;     // [nt][4][NH] HoT carried by each cell face (the solve's closure)
-    double* grad;     // [nt][NV][3] gradients of the primitives
+    double* hotf;     // [NH][nt][4] HoT carried by each cell face (the solve's closure)
+    double* rec;      // [nt][4 NV] cell records: primitives, then their gradients [NV][3]
     double* kn;       // [nt]
     uint8_t* avail;   // [nt]
     uint8_t* navail;  // [nt]
@@ -95,7 +117,7 @@ struct DigWork {
     double* mprev;    // [nt][NV] M^k
     double* Rs;       // [nt][NV] residual
     double* dt;       // [nt] pseudo-time step
-    double* U0;       // [nt][NV] conserved state at the start of an iteration
+    double* next;     // [nt][NV] state after an odd number of marching iterations (even: prim)
     double* stage;    // [nt][NV] stage state
     double* partial;  // [2 * blocks] reduction partials (blocks of the residual kernel: 4 lanes per cell)
     DigCtl* ctl;
@@ -112,19 +134,26 @@ struct DigWork {
 // rewma [4][nt]: the rotational moving-average sums of a rotating gas (else null)
 void launch_dig_sampled(hipStream_t s, const DigGeom& g, const double* ewma, const double* rewma, double FN, DigWork w);
 void launch_dig_kn(hipStream_t s, const DigGeom& g, DigWork w, double kn_ref, double T0, double rho0, double L0);
-void launch_dig_gradients(hipStream_t s, const DigGeom& g, const double* prim, double* grad, const DigCtl* ctl);
+void launch_dig_gradients(hipStream_t s, const DigGeom& g, const double* prim, double* rec, const DigCtl* ctl);
 void launch_dig_hot(hipStream_t s, const DigGeom& g, DigWork w);
-// Face HoT from cell HoT at prim (with `consistent`, corrected so that each
-// face's viscous stress at prim is the average of its cells' NSF + HoT).
-void launch_dig_face_hot(hipStream_t s, const DigGeom& g, const double* prim, const double* grad, const double* hot,
-                         double* hotf, int consistent);
+// Face HoT from cell HoT at the records' state (with `consistent`, corrected
+// so that each face's viscous stress there is the average of its cells' NSF +
+// HoT).
+void launch_dig_face_hot(hipStream_t s, const DigGeom& g, const double* rec, const double* hot, double* hotf,
+                         int consistent);
 void launch_dig_gate(hipStream_t s, const DigGeom& g, DigWork w, double kn_max, int passes);
 void launch_dig_ctl_reset(hipStream_t s, DigCtl* ctl);
 void launch_dig_copy(hipStream_t s, const double* src, double* dst, int64_t n);
-void launch_dig_residual(hipStream_t s, const DigGeom& g, const double* prim, const double* hotf, const double* grad,
-                         double* Rs, DigWork w, int first, double cfl);
-void launch_dig_iteration(hipStream_t s, const DigGeom& g, DigWork w, double cfl, double eps_m, int global_dt,
-                          int it);
+// Residual at the state of w.rec.
+void launch_dig_residual(hipStream_t s, const DigGeom& g, const double* hotf, double* Rs, DigWork w, int first,
+                         double cfl);
+// Iteration `it` of the marching from the state `base` to `out`.  A stopped
+// iteration (w.ctl: converged or failed) leaves w.ctl->iters at the number of
+// completed ones and its base as the last good state.
+void launch_dig_iteration(hipStream_t s, const DigGeom& g, DigWork w, const double* base, double* out, double cfl,
+                          double eps_m, int global_dt, int it);
+// w.prim = w.next; with ctl, counted and only if the iteration did not stop.
+void launch_dig_commit(hipStream_t s, const DigGeom& g, DigWork w, DigCtl* ctl);
 // Closed domain: scale the density of w.prim so that its total mass equals
 // the particles' (n_particles F_N m).
 void launch_dig_mass_rescale(hipStream_t s, const DigGeom& g, DigWork w, const Scalars* sc,

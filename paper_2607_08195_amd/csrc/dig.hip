@@ -5,9 +5,9 @@
 //   k_dig_grad      weighted least-squares gradients of the primitives
 //   k_dig_hot       NSF stress / heat flux and HoT = sampled - NSF
 //   k_dig_gate_*    admissibility gate and Jacobi reconstruction passes
-//   k_dig_save / k_dig_residual / k_dig_check / k_dig_update / k_dig_commit
-//                   one three-stage pseudo-time iteration of the
-//                   finite-volume macroscopic equations with frozen HoT
+//   k_dig_residual / k_dig_check
+//                   with k_dig_grad, one three-stage pseudo-time iteration of
+//                   the finite-volume macroscopic equations with frozen HoT
 //   k_dig_fb_*      particle feedback: target counts, shift-scale,
 //                   delete / clone
 //
@@ -33,9 +33,9 @@ template <int NV> struct Widths {
 
 __device__ __forceinline__ bool stopped(const DigCtl* ctl) { return ctl != nullptr && (ctl->conv | ctl->failed); }
 
-__device__ __forceinline__ double mu_of(const DigGeom& g, double T) { return g.mu_ref * pow(T / g.T_ref, g.omega); }
+__device__ __forceinline__ double mu_of(const DigGeom& g, double T) { return g.mu_ref * pow(g.T_ref.of(T), g.omega); }
 __device__ __forceinline__ double kappa_of(const DigGeom& g, double mu) {
-    return 15.0 * kBoltzmannDev * mu / (4.0 * g.mass);
+    return g.mass4.of(15.0 * kBoltzmannDev * mu);
 }
 // Translational and rotational conductivities of a rotating gas
 // (eq. thermal_conductivity_matrix): (mu R / 2) A^{-1} (5, d_r).
@@ -102,17 +102,18 @@ template <int NV>
 __device__ __forceinline__ bool prim_of(const DigGeom& g, const double* U, double* P) {
     if (!(U[0] > 0)) return false;
     P[0] = U[0];
-    P[1] = U[1] / U[0];
-    P[2] = U[2] / U[0];
-    P[3] = U[3] / U[0];
+    const Divisor rho(U[0]);
+    P[1] = rho.of(U[1]);
+    P[2] = rho.of(U[2]);
+    P[3] = rho.of(U[3]);
     const double uu = P[1] * P[1] + P[2] * P[2] + P[3] * P[3];
     if constexpr (NV == 6) {
-        const double er = U[5] / U[0];
-        P[4] = ((U[4] / U[0] - 0.5 * uu) - er) / (1.5 * g.R);
+        const double er = rho.of(U[5]);
+        P[4] = g.cv.of((rho.of(U[4]) - 0.5 * uu) - er);
         P[5] = er / ((0.5 * g.dr) * g.R);
         return P[4] > 0 && isfinite(P[4]) && P[5] > 0 && isfinite(P[5]);
     }
-    P[4] = (U[4] / U[0] - 0.5 * uu) / (1.5 * g.R);
+    P[4] = g.cv.of(rho.of(U[4]) - 0.5 * uu);
     return P[4] > 0 && isfinite(P[4]);
 }
 
@@ -175,18 +176,19 @@ __device__ __forceinline__ void central_flux(const DigGeom& g, const double* PL,
 // quotient.
 template <int NV>
 __device__ __forceinline__ void face_gradients(const double* gbase, const double* far, const double* near,
-                                               const double* dx, double dl, double* gu, double* gT, double* gTr) {
+                                               const double* dx, const Divisor& dl, double* gu, double* gT,
+                                               double* gTr) {
 #pragma unroll
     for (int v = 1; v < NV; ++v) {
         double gf[3], ga = 0.0;
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
             gf[j] = gbase[3 * v + j];
-            ga += gf[j] * dx[j] / dl;
+            ga += dl.of(gf[j] * dx[j]);
         }
-        const double jump = (far[v] - near[v]) / dl - ga;
+        const double jump = dl.of(far[v] - near[v]) - ga;
 #pragma unroll
-        for (int j = 0; j < 3; ++j) gf[j] += jump * dx[j] / dl;
+        for (int j = 0; j < 3; ++j) gf[j] += dl.of(jump * dx[j]);
         if (v < 4) {
 #pragma unroll
             for (int j = 0; j < 3; ++j) gu[3 * (v - 1) + j] = gf[j];
@@ -221,7 +223,7 @@ __device__ __forceinline__ void add_viscous(const double* vis, const double* n, 
 }
 
 template <int NV>
-__device__ __forceinline__ double viscous_rate(const DigGeom& g, double T, double rho, double dl) {
+__device__ __forceinline__ double viscous_rate(const DigGeom& g, double T, double rho, const Divisor& dl) {
     const double mu = mu_of(g, T);
     if constexpr (NV == 6) {
         double kt, kr;
@@ -230,10 +232,10 @@ __device__ __forceinline__ double viscous_rate(const DigGeom& g, double T, doubl
         const double dt_ = kt / (1.5 * rho * g.R), dr_ = kr / ((0.5 * g.dr) * rho * g.R);
         if (dt_ > d) d = dt_;
         if (dr_ > d) d = dr_;
-        return 2.0 * d / dl;
+        return dl.of(2.0 * d);
     }
     const double dmom = 4.0 * mu / (3.0 * rho), dth = kappa_of(g, mu) / (1.5 * rho * g.R);
-    return 2.0 * (dmom > dth ? dmom : dth) / dl;
+    return dl.of(2.0 * (dmom > dth ? dmom : dth));
 }
 
 // Rotational relaxation source of rho e_r (eq. macro):
@@ -363,67 +365,159 @@ __device__ __forceinline__ bool idle_cell(const DigGeom& g, int c) {
     return g.skip_idle && !g.cases[g.cell_case[c]].enabled;
 }
 
-// One lane per (cell, face), four consecutive lanes per cell: each lane
-// forms its face's weighted difference terms; the cell's sums are taken over
-// the four lanes in face order (a face without a value adds +0, which leaves
-// the sum unchanged), and each lane writes a quarter of the gradient.
+// Orders this wave's LDS accesses (the LDS serves one wave's in program
+// order, so only the compiler has to be held).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The kernels below work a lane per (cell, face), four consecutive lanes per
+// cell, sixteen cells per wave.  A lane needs the values of the cell behind
+// its face: read lane by lane, 16 bytes at a time, each load instruction
+// touches 64 lines and the vector L1's access rate bounds the kernel.  Here
+// the wave reads the records together, consecutive lanes consecutive parts T
+// (n of them a record), and hands them out through LDS: record r < 64 is that
+// of cell `nb` of lane r, record 64 + q that of the wave's q-th cell c0 + q.
+// Part k of record r goes to lds[n r + swz(r, k)].  Parts are counted in 32
+// bits (a face link leaves 28 bits for the cell, n is at most 12).
+template <class T, int n, class Swz>
+__device__ __forceinline__ void gather_records(const T* rec, int nb, int c0, int nt, T* lds, Swz&& swz) {
+    const int lane = threadIdx.x & 63;
+    constexpr int kOwn = (16 * n + 63) / 64;
+    T v[n], o[kOwn];
+    const uint32_t first = (uint32_t)nb * n, own = (uint32_t)c0 * n, last = (uint32_t)nt * n - 1;
+#pragma unroll
+    for (int k = 0; k < n; ++k) {
+        const int e = lane + 64 * k, r = e / n;
+        v[k] = rec[(uint32_t)__shfl((int)first, r, 64) + (uint32_t)(e - r * n)];
+    }
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) {
+        o[k] = rec[min(own + min(lane + 64 * k, 16 * n - 1), last)];
+    }
+#pragma unroll
+    for (int k = 0; k < n; ++k) {
+        const int e = lane + 64 * k, r = e / n;
+        lds[n * r + swz(r, e - r * n)] = v[k];
+    }
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) {
+        // (lanes past the last part write it again: no branch, behind which
+        // the load would be put)
+        const int e = min(lane + 64 * k, 16 * n - 1), r = 64 + e / n;
+        lds[n * r + swz(r, e - (r - 64) * n)] = o[k];
+    }
+}
+
+// The cell behind a face link (the cell itself where there is none).
+__device__ __forceinline__ int link_cell(int link, int c) {
+    const int kind = link & 7;
+    return kind == kLinkInterior || kind == kLinkPeriodic ? link >> 3 : c;
+}
+
+// Weighted least-squares gradients into the cell records rec[nt][4 NV] =
+// primitives, then their gradients [NV][3] (what the residual kernel reads
+// of a neighbour, in one piece).  Each lane forms its face's weighted
+// difference terms; they change hands in LDS, each lane summing those of one
+// variable over the four faces in face order (a face without a value adds
+// +0, which leaves the sum unchanged).  The records leave through LDS in
+// 16-byte pieces.  On 384,000 cells 35 us
+// (67 lane by lane, the terms exchanged by shuffles), near the 160 B a cell
+// written and 40 read at the card's copy rate (15 us) and their latency.
 template <int NV>
-__global__ __launch_bounds__(kDigThreads) void k_dig_grad(DigGeom g, const double* prim, double* grad, const DigCtl* ctl) {
+__global__ __launch_bounds__(kDigThreads) void k_dig_grad(DigGeom g, const double* prim, double* rec, const DigCtl* ctl) {
     if (stopped(ctl)) return;
+    constexpr int kT = 3 * NV;  // terms of a face
+    constexpr int kR = 4 * NV;  // a record
+    static_assert(64 * kT >= 80 * NV && 64 * kT >= 16 * kR, "the terms' space serves all three uses");
+    __shared__ __align__(16) double lds[kDigThreads / 64][64 * kT + 16 * 9];
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int c = (int)(t >> 2), f = (int)(t & 3);
+    const int lane = threadIdx.x & 63, q = lane >> 2, c0 = c - q;
     const bool live = c < g.nt && !idle_cell(g, c);
-    double tb[NV][3];
+    const size_t nf = 4 * (size_t)g.nt;
+    double* L0 = lds[threadIdx.x >> 6];
+    double* Lm = L0 + 64 * kT;  // least-squares matrices of the wave's cells
+    const int link = c < g.nt ? g.flink[t] : kLinkOutflow;
+    double d[3] = {1.0, 0.0, 0.0}, lm[3];
+    if (c < g.nt) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) tb[v][0] = tb[v][1] = tb[v][2] = 0.0;
-    if (live) {
-        const int link = g.flink[4 * (size_t)c + f];
-        const int kind = link & 7, idx = link >> 3;
-        const bool inner = kind == kLinkInterior || kind == kLinkPeriodic;
-        if (inner || kind == kLinkWall) {
-            double pc[NV], far[NV];
-#pragma unroll
-            for (int v = 0; v < NV; ++v) pc[v] = prim[NV * (size_t)c + v];
-            if (inner) {
-#pragma unroll
-                for (int v = 0; v < NV; ++v) far[v] = prim[NV * (size_t)idx + v];
-            } else {
-                const DigGroup& gr = g.groups[idx];
-                far[0] = pc[0];
-                far[1] = gr.u[0]; far[2] = gr.u[1]; far[3] = gr.u[2];
-                far[4] = gr.T;
-                if constexpr (NV == 6) far[5] = gr.T;
-            }
-            const double* dx = g.fdx + 12 * (size_t)c + 3 * f;
-            const double d0 = dx[0], d1 = dx[1], d2 = dx[2];
-            const double wgt = 1.0 / (d0 * d0 + d1 * d1 + d2 * d2);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                const double dphi = far[v] - pc[v];
-                tb[v][0] = wgt * d0 * dphi;
-                tb[v][1] = wgt * d1 * dphi;
-                tb[v][2] = wgt * d2 * dphi;
-            }
-        }
+        for (int i = 0; i < 3; ++i) d[i] = g.fdx[i * nf + t];
     }
-    const int q0 = (int)(threadIdx.x & 63) & ~3;
-    double b[NV][3];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) b[v][0] = b[v][1] = b[v][2] = 0.0;
+    for (int k = 0; k < 3; ++k)
+        lm[k] = g.lsq[min((int64_t)9 * c0 + min(lane + 64 * k, 16 * 9 - 1), (int64_t)9 * g.nt - 1)];
+    gather_records<double, NV>(prim, c < g.nt ? link_cell(link, c) : 0, c0, g.nt, L0, [](int, int k) { return k; });
+#pragma unroll
+    for (int k = 0; k < 3; ++k) Lm[min(lane + 64 * k, 16 * 9 - 1)] = lm[k];
+    wave_sync();
+    double pc[NV], far[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        pc[v] = L0[64 * NV + q * NV + v];
+        far[v] = L0[lane * NV + v];
+    }
+    wave_sync();
+    const int kind = link & 7;
+    const bool inner = kind == kLinkInterior || kind == kLinkPeriodic;
+    if (!inner && kind == kLinkWall) {
+        const DigGroup& gr = g.groups[link >> 3];
+        far[0] = pc[0];
+        far[1] = gr.u[0]; far[2] = gr.u[1]; far[3] = gr.u[2];
+        far[4] = gr.T;
+        if constexpr (NV == 6) far[5] = gr.T;
+    }
+    const bool has = live && (inner || kind == kLinkWall);
+    const double wgt = 1.0 / (d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const double dphi = far[v] - pc[v];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) L0[kT * lane + 3 * v + i] = has ? wgt * d[i] * dphi : 0.0;
+    }
+    wave_sync();
+    // lane f: gradient f, and of the (NV - 4) others' components every fourth
+    double b[3] = {0.0, 0.0, 0.0}, l[9], o[3];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) l[k] = Lm[9 * q + k];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int v = 0; v < NV; ++v)
+        for (int i = 0; i < 3; ++i) b[i] += L0[kT * (4 * q + k) + 3 * f + i];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) b[v][i] += __shfl(tb[v][i], q0 + k, 64);
-    if (!live) return;
-    const double* L = g.lsq + 9 * (size_t)c;
-    double* o = grad + 3 * NV * (size_t)c;
+    for (int i = 0; i < 3; ++i) o[i] = l[3 * i] * b[0] + l[3 * i + 1] * b[1] + l[3 * i + 2] * b[2];
+    constexpr int kMore = (3 * (NV - 4) + 3) / 4;
+    double x[kMore];
+#pragma unroll
+    for (int m = 0; m < kMore; ++m) {
+        const int e = min(f + 4 * m, 3 * (NV - 4) - 1), v = 4 + e / 3, i = e % 3;
+        double s[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) s[j] += L0[kT * (4 * q + k) + 3 * v + j];
+        const double l0 = Lm[9 * q + 3 * i], l1 = Lm[9 * q + 3 * i + 1], l2 = Lm[9 * q + 3 * i + 2];
+        x[m] = l0 * s[0] + l1 * s[1] + l2 * s[2];
+    }
+    wave_sync();
 #pragma unroll
     for (int v = 0; v < NV; ++v)
+        if (v % 4 == f) L0[kR * q + v] = pc[v];
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
-            if ((3 * v + i) % 4 == f) o[3 * v + i] = L[3 * i] * b[v][0] + L[3 * i + 1] * b[v][1] + L[3 * i + 2] * b[v][2];
+    for (int i = 0; i < 3; ++i) L0[kR * q + NV + 3 * f + i] = o[i];
+#pragma unroll
+    for (int m = 0; m < kMore; ++m)
+        if (f + 4 * m < 3 * (NV - 4)) L0[kR * q + NV + 12 + f + 4 * m] = x[m];
+    wave_sync();
+    const int n2 = min(16, g.nt - c0) * (kR / 2);  // (a wave past the last cell: none)
+    double2* out = (double2*)(rec + (size_t)kR * min(c0, g.nt));
+#pragma unroll
+    for (int k = 0; k < (16 * kR / 2 + 63) / 64; ++k) {
+        const int e = lane + 64 * k;
+        if (e < n2) out[e] = ((const double2*)L0)[e];
+    }
 }
 
 // HoT = (sigma, q)_sampled - (sigma, q)_NSF at the sampled state
@@ -433,7 +527,7 @@ __global__ void k_dig_hot(DigGeom g, DigWork w) {
     constexpr int NH = Widths<NV>::NH, NS = Widths<NV>::NS;
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= g.nt) return;
-    const double* gr = w.grad + 3 * NV * (size_t)c;
+    const double* gr = w.rec + 4 * NV * (size_t)c + NV;
     double nsf[NH];
     nsf_local<NV>(g, w.prim[NV * (size_t)c + 4], gr + 3, gr + 12, gr + 15, nsf);
     const bool ok = w.ok[c];
@@ -456,56 +550,68 @@ __device__ __forceinline__ void wall_state(const DigGroup& gr, const double* Pc,
     if constexpr (NV == 6) wv[5] = gr.T;
 }
 
-// HoT carried by each cell face: the cell HoT averaged to the face (the
-// cell's own at a diffuse wall); with `consistent`, plus the cell NSF
-// stresses averaged to the face minus the face NSF stress of the viscous
-// flux, both at prim, so that at prim each face's viscous stress is the
-// average of its cells' NSF + HoT.
+// HoT carried by each cell face (hotf[NH][4 nt]): the cell HoT averaged to
+// the face (the cell's own at a diffuse wall); with `consistent`, plus the
+// cell NSF stresses averaged to the face minus the face NSF stress of the
+// viscous flux, both at the records' state, so that there each face's
+// viscous stress is the average of its cells' NSF + HoT.  One lane per
+// (cell, face).
 template <int NV>
-__global__ void k_dig_face_hot(DigGeom g, const double* prim, const double* grad, const double* hot, double* hotf,
-                               int consistent) {
+__global__ __launch_bounds__(kDigThreads) void k_dig_face_hot(DigGeom g, const double* rec, const double* hot,
+                                                              double* hotf, int consistent) {
     constexpr int NH = Widths<NV>::NH, NG = Widths<NV>::NG;
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int c = (int)(t >> 2);
     if (c >= g.nt) return;
+    const size_t nf = 4 * (size_t)g.nt;
+    const int link = g.flink[t];
+    const int kind = link & 7, idx = link >> 3;
+    double* h = hotf + t;
+    const bool inner = kind == kLinkInterior || kind == kLinkPeriodic;
+    if (!inner && kind != kLinkWall) {
+        for (int k = 0; k < NH; ++k) h[k * nf] = 0.0;
+        return;
+    }
     double Pc[NV], gc[NG], nc[NH];
-    for (int v = 0; v < NV; ++v) Pc[v] = prim[NV * (size_t)c + v];
-    for (int k = 0; k < NG; ++k) gc[k] = grad[NG * (size_t)c + k];
+    const double* R = rec + 4 * NV * (size_t)c;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) Pc[v] = R[v];
+#pragma unroll
+    for (int k = 0; k < NG; ++k) gc[k] = R[NV + k];
     nsf_local<NV>(g, Pc[4], gc + 3, gc + 12, gc + 15, nc);
-    for (int f = 0; f < 4; ++f) {
-        const int link = g.flink[4 * c + f];
-        const int kind = link & 7, idx = link >> 3;
-        const size_t fo = 12 * (size_t)c + 3 * f;
-        const double dx[3] = {g.fdx[fo], g.fdx[fo + 1], g.fdx[fo + 2]};
-        const double dl = sqrt(dx[0] * dx[0] + dx[1] * dx[1] + dx[2] * dx[2]);
-        double* h = hotf + 4 * NH * (size_t)c + NH * f;
-        double gu[9], gT[3], gTr[3], vf[NH];
-        if (kind == kLinkInterior || kind == kLinkPeriodic) {
-            const int nb = idx;
-            double Pn[NV], gn[NG], gavg[NG], nn[NH];
-            for (int v = 0; v < NV; ++v) Pn[v] = prim[NV * (size_t)nb + v];
-            for (int k = 0; k < NG; ++k) gn[k] = grad[NG * (size_t)nb + k];
-            for (int k = 0; k < NG; ++k) gavg[k] = 0.5 * (gc[k] + gn[k]);
-            face_gradients<NV>(gavg, Pn, Pc, dx, dl, gu, gT, gTr);
-            nsf_local<NV>(g, 0.5 * (Pc[4] + Pn[4]), gu, gT, gTr, vf);
-            nsf_local<NV>(g, Pn[4], gn + 3, gn + 12, gn + 15, nn);
-            for (int k = 0; k < NH; ++k) {
-                double v = 0.5 * (hot[NH * (size_t)c + k] + hot[NH * (size_t)nb + k]);
-                if (consistent) v += 0.5 * (nc[k] + nn[k]) - vf[k];
-                h[k] = v;
-            }
-        } else if (kind == kLinkWall) {
-            const DigGroup& gr = g.groups[idx];
-            double wallv[NV];
-            wall_state<NV>(gr, Pc, wallv);
-            face_gradients<NV>(gc, wallv, Pc, dx, dl, gu, gT, gTr);
-            nsf_local<NV>(g, gr.T, gu, gT, gTr, vf);
-            for (int k = 0; k < NH; ++k) {
-                double v = hot[NH * (size_t)c + k];
-                if (consistent) v += nc[k] - vf[k];
-                h[k] = v;
-            }
-        } else {
-            for (int k = 0; k < NH; ++k) h[k] = 0.0;
+    const double dx[3] = {g.fdx[t], g.fdx[nf + t], g.fdx[2 * nf + t]};
+    const Divisor dl(sqrt(dx[0] * dx[0] + dx[1] * dx[1] + dx[2] * dx[2]));
+    double gu[9], gT[3], gTr[3], vf[NH];
+    if (inner) {
+        const int nb = idx;
+        double Pn[NV], gn[NG], gavg[NG], nn[NH];
+        const double* Rn = rec + 4 * NV * (size_t)nb;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) Pn[v] = Rn[v];
+#pragma unroll
+        for (int k = 0; k < NG; ++k) gn[k] = Rn[NV + k];
+#pragma unroll
+        for (int k = 0; k < NG; ++k) gavg[k] = 0.5 * (gc[k] + gn[k]);
+        face_gradients<NV>(gavg, Pn, Pc, dx, dl, gu, gT, gTr);
+        nsf_local<NV>(g, 0.5 * (Pc[4] + Pn[4]), gu, gT, gTr, vf);
+        nsf_local<NV>(g, Pn[4], gn + 3, gn + 12, gn + 15, nn);
+#pragma unroll
+        for (int k = 0; k < NH; ++k) {
+            double v = 0.5 * (hot[NH * (size_t)c + k] + hot[NH * (size_t)nb + k]);
+            if (consistent) v += 0.5 * (nc[k] + nn[k]) - vf[k];
+            h[k * nf] = v;
+        }
+    } else {
+        const DigGroup& gr = g.groups[idx];
+        double wallv[NV];
+        wall_state<NV>(gr, Pc, wallv);
+        face_gradients<NV>(gc, wallv, Pc, dx, dl, gu, gT, gTr);
+        nsf_local<NV>(g, gr.T, gu, gT, gTr, vf);
+#pragma unroll
+        for (int k = 0; k < NH; ++k) {
+            double v = hot[NH * (size_t)c + k];
+            if (consistent) v += nc[k] - vf[k];
+            h[k * nf] = v;
         }
     }
 }
@@ -599,6 +705,8 @@ __global__ void k_dig_ctl_reset(DigCtl* ctl) {
     ctl->dtmin = 0.0;
     ctl->conv = 0;
     ctl->failed = 0;
+    ctl->failed1 = 0;
+    ctl->failed2 = 0;
     ctl->iters = 0;
     ctl->n_rejected = 0;
     ctl->n_reconstructed = 0;
@@ -617,52 +725,100 @@ __global__ void k_dig_copy(const double* src, double* dst, int64_t n) {
 // finite-volume residual: R_c = sum_f (F_inviscid + F_viscous).n A_f
 // (minus V times the relaxation source in the rho e_r equation)
 // ---------------------------------------------------------------------------
-// One lane per (cell, face), four consecutive lanes per cell: each lane
-// computes its face's flux; the cell's sums are then formed from the four
-// lanes' terms in face order (the order of a loop over the faces), so that
-// four times as many lanes keep the gathered neighbour loads in flight.
-template <int NV>
-__global__ __launch_bounds__(kDigThreads) void k_dig_residual(DigGeom g, const double* prim, const double* hotf,
-                                                              const double* grad, double* Rs, DigWork w, int first,
-                                                              double cfl) {
+// One lane per (cell, face): each lane computes its face's flux; the cell's
+// sums are then formed from the four lanes' terms in face order (the order
+// of a loop over the faces), so that four times as many lanes keep the loads
+// in flight.  The records of the cells behind the faces are gathered by the
+// wave (gather_records).
+// The terms change hands in LDS and the workgroup's first wave ends the work,
+// a lane per cell.  With UPDATE it goes on to the stage update
+// U = U0 - alpha dt / V R (U0 from the iteration's first state `base`, the
+// new state to `out`, dt the local step); without, the residual goes to Rs.
+// FIRST: an iteration's first stage, which sets dt and the partial sums of
+// the norm.  Bounded by its vector instructions (1,280 per face, of which pow
+// is 220: 0.7 of the time) with the three waves per SIMD that the registers
+// and the LDS allow.  On 384,000 cells 84 us, 89 the first stage, where
+// residual, save, update and commit by themselves took 92, 17, 13 and 14.
+template <int NV, bool UPDATE, bool FIRST>
+__global__ __launch_bounds__(kDigThreads, NV == 6 ? 2 : 3) void k_dig_residual(DigGeom g, const double* rec,
+                                                                              const double* hotf, double* Rs,
+                                                                              DigWork w, double cfl,
+                                                                              const double* base, double* out,
+                                                                              double alpha) {
     constexpr int NH = Widths<NV>::NH, NG = Widths<NV>::NG;
     if (stopped(w.ctl)) return;
+    __shared__ double2 lds[kDigThreads / 64][80 * 2 * NV + 8 * NV];
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = (int)(t >> 2), f = (int)(t & 3);
+    const int c = (int)(t >> 2);
+    const int lane = threadIdx.x & 63;
     const bool live = c < g.nt && !idle_cell(g, c);
+    const size_t nf = 4 * (size_t)g.nt;
+    const int link = c < g.nt ? g.flink[t] : kLinkOutflow;
+    const int kind = link & 7, idx = link >> 3;
+    const bool inner = kind == kLinkInterior || kind == kLinkPeriodic;
+    // the face's own data is asked for before the records, in one latency
+    const size_t tf = min((size_t)t, nf - 1), cf = tf >> 2;
+    const double n[3] = {g.fnu[tf], g.fnu[nf + tf], g.fnu[2 * nf + tf]};
+    const double dx[3] = {g.fdx[tf], g.fdx[nf + tf], g.fdx[2 * nf + tf]};
+    const double xf[3] = {g.fcen[tf], g.fcen[nf + tf], g.fcen[2 * nf + tf]};
+    const double xc[3] = {g.cen[3 * cf], g.cen[3 * cf + 1], g.cen[3 * cf + 2]};
+    const double A = g.farea[tf];
+    double hf[NH];
+#pragma unroll
+    for (int k = 0; k < NH; ++k) hf[k] = hotf[k * nf + tf];
+    double2* L0 = lds[threadIdx.x >> 6];
+    double* Lb = (double*)(L0 + 80 * 2 * NV);  // first states of the wave's cells
+    double bs[2], vol = 1.0, dtc = 0.0;
+    if constexpr (UPDATE) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            bs[k] = base[min((int64_t)NV * (c - (lane >> 2)) + min(lane + 64 * k, 16 * NV - 1), (int64_t)NV * g.nt - 1)];
+    }
+    const int cw = blockIdx.x * (kDigThreads / 4) + lane;  // the first wave's cells
+    if (threadIdx.x < 64 && cw < g.nt) {
+        vol = g.vol[cw];
+        if constexpr (UPDATE && !FIRST) dtc = w.dt[cw];
+    }
+    // records of this cell and of the one behind the face (a face without a
+    // neighbour cell reads its own cell's, unused); the order of a record's
+    // parts keeps eight lanes' 16-byte reads on different banks
+    double Pc[NV], gc[NG], Pn[NV], gn[NG];
+    auto swz = [](int r, int k) { return NV == 6 ? k ^ ((r >> 1) & 3) : k ^ ((r >> 2) & 1); };
+    {
+        gather_records<double2, 2 * NV>((const double2*)rec, c < g.nt ? link_cell(link, c) : 0, c - (lane >> 2), g.nt,
+                                        L0, swz);
+        if constexpr (UPDATE) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) Lb[min(lane + 64 * k, 16 * NV - 1)] = bs[k];
+        }
+        wave_sync();
+        const int ro = 64 + (lane >> 2);
+#pragma unroll
+        for (int k = 0; k < 2 * NV; ++k) {
+            const double2 x = L0[2 * NV * lane + swz(lane, k)], y = L0[2 * NV * ro + swz(ro, k)];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int e = 2 * k + h;
+                const double xn = h ? x.y : x.x, xc = h ? y.y : y.x;
+                if (e < NV) {
+                    Pn[e < NV ? e : 0] = xn;
+                    Pc[e < NV ? e : 0] = xc;
+                } else {
+                    gn[e < NV ? 0 : e - NV] = xn;
+                    gc[e < NV ? 0 : e - NV] = xc;
+                }
+            }
+        }
+    }
     double FA[NV], SA = 0.0;
 #pragma unroll
     for (int v = 0; v < NV; ++v) FA[v] = 0.0;
-    double Pc[NV];
     if (live) {
-        double gc[NG];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) Pc[v] = prim[NV * (size_t)c + v];
-#pragma unroll
-        for (int k = 0; k < NG; ++k) gc[k] = grad[NG * (size_t)c + k];
-        const double xc[3] = {g.cen[3 * (size_t)c], g.cen[3 * (size_t)c + 1], g.cen[3 * (size_t)c + 2]};
-        const int link = g.flink[4 * (size_t)c + f];
-        const int kind = link & 7, idx = link >> 3;
-        const bool inner = kind == kLinkInterior || kind == kLinkPeriodic;
-        // the neighbour's state and gradients are requested with the face's
-        // geometry (a face without a neighbour cell reads its own cell's,
-        // unused)
-        const size_t nb = inner ? (size_t)idx : (size_t)c;
-        double Pn[NV], gn[NG];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) Pn[v] = prim[NV * nb + v];
-#pragma unroll
-        for (int k = 0; k < NG; ++k) gn[k] = grad[NG * nb + k];
-        const size_t fo = 12 * (size_t)c + 3 * f;
-        const double n[3] = {g.fnu[fo], g.fnu[fo + 1], g.fnu[fo + 2]};
-        const double dx[3] = {g.fdx[fo], g.fdx[fo + 1], g.fdx[fo + 2]};
-        const double A = g.farea[4 * (size_t)c + f];
         double F[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) F[v] = 0.0;
         double lam = 0.0, lamv = 0.0;
         if (inner) {
-            const double xf[3] = {g.fcen[fo], g.fcen[fo + 1], g.fcen[fo + 2]};
             double rc[3], rn[3];
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
@@ -686,7 +842,7 @@ __global__ __launch_bounds__(kDigThreads) void k_dig_residual(DigGeom g, const d
             }
             central_flux<NV>(g, PL, PR, n, F, lam);
             const double d2 = dx[0] * dx[0] + dx[1] * dx[1] + dx[2] * dx[2];
-            const double dl = sqrt(d2);
+            const Divisor dl(sqrt(d2));
             double gavg[NG];
 #pragma unroll
             for (int k = 3; k < NG; ++k) gavg[k] = 0.5 * (gc[k] + gn[k]);
@@ -696,12 +852,11 @@ __global__ __launch_bounds__(kDigThreads) void k_dig_residual(DigGeom g, const d
             const double rf = 0.5 * (Pc[0] + Pn[0]);
             double vis[NH];
             nsf_local<NV>(g, Tf, gu, gT, gTr, vis);
-            const double* hf = hotf + 4 * NH * (size_t)c + NH * f;
 #pragma unroll
             for (int k = 0; k < NH; ++k) vis[k] += hf[k];
             const double uf[3] = {0.5 * (Pc[1] + Pn[1]), 0.5 * (Pc[2] + Pn[2]), 0.5 * (Pc[3] + Pn[3])};
             add_viscous<NV>(vis, n, uf, F);
-            lamv = viscous_rate<NV>(g, Tf, rf, dl);
+            if constexpr (FIRST) lamv = viscous_rate<NV>(g, Tf, rf, dl);
         } else if (kind == kLinkWall || kind == kLinkSpecular) {
             const double p = Pc[0] * g.R * Pc[4];
 #pragma unroll
@@ -710,18 +865,17 @@ __global__ __launch_bounds__(kDigThreads) void k_dig_residual(DigGeom g, const d
             if (kind == kLinkWall) {
                 const DigGroup& gr = g.groups[idx];
                 const double d2 = dx[0] * dx[0] + dx[1] * dx[1] + dx[2] * dx[2];
-                const double dl = sqrt(d2);
+                const Divisor dl(sqrt(d2));
                 double wallv[NV];
                 wall_state<NV>(gr, Pc, wallv);
                 double gu[9], gT[3], gTr[3];
                 face_gradients<NV>(gc, wallv, Pc, dx, dl, gu, gT, gTr);
                 double vis[NH];
                 nsf_local<NV>(g, gr.T, gu, gT, gTr, vis);
-                const double* hf = hotf + 4 * NH * (size_t)c + NH * f;
 #pragma unroll
                 for (int k = 0; k < NH; ++k) vis[k] += hf[k];
                 add_viscous<NV>(vis, n, gr.u, F);
-                lamv = viscous_rate<NV>(g, gr.T, Pc[0], dl);
+                if constexpr (FIRST) lamv = viscous_rate<NV>(g, gr.T, Pc[0], dl);
             }
         } else if (kind == kLinkInflow) {
             const DigGroup& gr = g.groups[idx];
@@ -737,42 +891,94 @@ __global__ __launch_bounds__(kDigThreads) void k_dig_residual(DigGeom g, const d
         for (int v = 0; v < NV; ++v) FA[v] = F[v] * A;
         SA = (lam + lamv) * A;
     }
-    // the cell's sums over its four lanes, in face order (every lane of the
-    // wave takes part in the exchange)
-    const int q0 = (int)(threadIdx.x & 63) & ~3;
-    double Rc[NV];
+    // the terms into the space of the neighbours' records, one of 64 lanes'
+    // after another
+    wave_sync();
 #pragma unroll
-    for (int v = 0; v < NV; ++v) Rc[v] = 0.0;
-    double sp = 0.0;
+    for (int v = 0; v < NV; ++v) ((double*)L0)[64 * v + lane] = FA[v];
+    if constexpr (FIRST) ((double*)L0)[64 * NV + lane] = SA;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const int q = lane & 15;
+    const double2* Lx = lds[lane >> 4];
+    auto face_sum = [&](int v) {
+        const double2 a = Lx[32 * v + 2 * q], b = Lx[32 * v + 2 * q + 1];
+        return 0.0 + a.x + a.y + b.x + b.y;
+    };
+    double R[NV], sp = 0.0, r2 = 0.0, dtmin = __builtin_inf();
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int v = 0; v < NV; ++v) R[v] = face_sum(v);
+    if constexpr (FIRST) sp = face_sum(NV);
+    const bool mine = cw < g.nt, run = mine && !idle_cell(g, cw);
+    if constexpr (NV == 6) {
+        if (run) {
+            double P0[NV], rate;
 #pragma unroll
-        for (int v = 0; v < NV; ++v) Rc[v] += __shfl(FA[v], q0 + k, 64);
-        sp += __shfl(SA, q0 + k, 64);
-    }
-    double r2 = 0.0, dtc = __builtin_inf();
-    if (live && f == 0) {
-        if constexpr (NV == 6) {
-            double rate;
-            const double src = relax_source(g, Pc, rate);
-            Rc[5] -= g.vol[c] * src;
-            sp += g.vol[c] * rate;
+            for (int v = 0; v < NV; ++v)
+                P0[v] = ((const double*)(Lx + 2 * NV * (64 + q) + swz(64 + q, v / 2)))[v % 2];
+            const double src = relax_source(g, P0, rate);
+            R[5] -= vol * src;
+            sp += vol * rate;
         }
-#pragma unroll
-        for (int v = 0; v < NV; ++v) Rs[NV * (size_t)c + v] = Rc[v];
-        if (first) {
-            dtc = cfl * g.vol[c] / sp;
-            w.dt[c] = dtc;
-            r2 = Rc[0] * Rc[0];
+    }
+    if constexpr (FIRST) {
+        if (run) {
+            dtc = cfl * vol / sp;
+            w.dt[cw] = dtc;
+            dtmin = dtc;
+            r2 = R[0] * R[0];
             if constexpr (NV == 6) {
                 // the rotational-energy residual in mass units, R_er / (R T0)
-                const double ert = g.cases ? g.R * g.cases[g.cell_case[c]].T0 : g.ert;
-                const double r5 = Rc[5] / ert;
+                const double ert = g.cases ? g.R * g.cases[g.cell_case[cw]].T0 : g.ert;
+                const double r5 = R[5] / ert;
                 r2 = r2 + r5 * r5;
             }
         }
+        // a fixed tree
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            r2 += __shfl_down(r2, o, 64);
+            dtmin = fmin(dtmin, __shfl_down(dtmin, o, 64));
+        }
+        if (lane == 0) {
+            w.partial[2 * blockIdx.x] = r2;
+            w.partial[2 * blockIdx.x + 1] = dtmin;
+        }
     }
-    if (first) block_sum_min(r2, dtc, &w.partial[2 * blockIdx.x], &w.partial[2 * blockIdx.x + 1]);
+    if (!UPDATE && g.skip_idle) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            if (run) Rs[NV * (size_t)cw + v] = R[v];
+        return;
+    }
+    double* O = (double*)lds[0] + 64 * (NV + 1);  // the cells' values, for whole-line stores
+    if constexpr (UPDATE) {
+        double B[NV], P[NV], U[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) B[v] = ((const double*)(Lx + 80 * 2 * NV))[NV * q + v];
+        cons_of<NV>(g, B, U);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) U[v] = U[v] - alpha * dtc / vol * R[v];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) P[v] = B[v];
+        const bool ok = prim_of<NV>(g, U, P);
+        // Not physical: the iteration counts for nothing.  The flag is raised
+        // to a stop by the next convergence test, not here, where the
+        // workgroup's other waves could come to see it; that test decides
+        // whether a first stage's failure counts.
+        if (run && !ok) atomicOr(FIRST ? &w.ctl->failed1 : &w.ctl->failed2, 1);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) O[NV * lane + v] = run ? P[v] : B[v];
+    } else {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) O[NV * lane + v] = R[v];
+    }
+    wave_sync();
+    double* to = UPDATE ? out : Rs;
+    const int64_t o0 = (int64_t)NV * (cw - lane), on = (int64_t)NV * g.nt;
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+        if (o0 + 64 * v + lane < on) to[o0 + 64 * v + lane] = O[64 * v + lane];
 }
 
 // Density residual norm (with rotation: and the rotational-energy residual),
@@ -780,6 +986,11 @@ __global__ __launch_bounds__(kDigThreads) void k_dig_residual(DigGeom g, const d
 // (single workgroup).
 __global__ __launch_bounds__(kDigThreads) void k_dig_check(DigWork w, int nblk, int it, double eps_m) {
     if (stopped(w.ctl)) return;
+    if (w.ctl->failed2) {  // the last iteration came to nothing
+        __syncthreads();
+        if (threadIdx.x == 0) w.ctl->failed = 1;
+        return;
+    }
     double s = 0.0, m = __builtin_inf();
     for (int b = threadIdx.x; b < nblk; b += kDigThreads) {
         s += w.partial[2 * b];
@@ -792,59 +1003,46 @@ __global__ __launch_bounds__(kDigThreads) void k_dig_check(DigWork w, int nblk, 
         DigCtl* ctl = w.ctl;
         const double res = sqrt(tot);
         ctl->res = res;
+        ctl->iters = it;  // completed ones: an iteration that fails does not reach the next test
         if (it == 0) ctl->res0 = res;
         const double res0 = ctl->res0;
-        if (!(res0 > 0) || res <= eps_m * res0) ctl->conv = 1;
+        if (!(res0 > 0) || res <= eps_m * res0)
+            ctl->conv = 1;
+        else if (ctl->failed1)
+            ctl->failed = 1;
         ctl->dtmin = mn;
     }
 }
 
+// Stage update U = U0 - alpha dtmin / V R(stage) with one step for all cells
+// (known only after the residual kernel).
 template <int NV>
-__global__ void k_dig_save(DigGeom g, DigWork w) {
+__global__ void k_dig_update(DigGeom g, DigWork w, double alpha, const double* base, double* out) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= g.nt || stopped(w.ctl) || idle_cell(g, c)) return;
-    double P[NV], U[NV];
+    const double dtc = w.ctl->dtmin;
+    double B[NV], U[NV], P[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        P[v] = w.prim[NV * (size_t)c + v];
-        w.stage[NV * (size_t)c + v] = P[v];
+    for (int v = 0; v < NV; ++v) B[v] = base[NV * (size_t)c + v];
+    cons_of<NV>(g, B, U);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) U[v] = U[v] - alpha * dtc / g.vol[c] * w.Rs[NV * (size_t)c + v];
+    const bool ok = prim_of<NV>(g, U, P);
+    if (ok || U[0] > 0) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) out[NV * (size_t)c + v] = P[v];
     }
-    cons_of<NV>(g, P, U);
-#pragma unroll
-    for (int v = 0; v < NV; ++v) w.U0[NV * (size_t)c + v] = U[v];
+    if (!ok) atomicOr(&w.ctl->failed, 1);
 }
 
-// Stage update U = U0 - alpha dt / V R(stage).
+// prim = next, unless the iteration stopped (ctl not null; idle cells keep
+// their state).
 template <int NV>
-__global__ void k_dig_update(DigGeom g, DigWork w, double alpha, int global_dt) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= g.nt || stopped(w.ctl) || idle_cell(g, c)) return;
-    const double dtc = global_dt ? w.ctl->dtmin : w.dt[c];
-    double U[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v)
-        U[v] = w.U0[NV * (size_t)c + v] - alpha * dtc / g.vol[c] * w.Rs[NV * (size_t)c + v];
-    double P[NV];
-    if (prim_of<NV>(g, U, P)) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) w.stage[NV * (size_t)c + v] = P[v];
-    } else {
-        if (U[0] > 0) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) w.stage[NV * (size_t)c + v] = P[v];
-        }
-        atomicOr(&w.ctl->failed, 1);
-    }
-}
-
-template <int NV>
-__global__ void k_dig_commit(DigGeom g, DigWork w) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= g.nt || stopped(w.ctl)) return;
-    if (c == 0) w.ctl->iters += 1;
-    if (idle_cell(g, c)) return;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) w.prim[NV * (size_t)c + v] = w.stage[NV * (size_t)c + v];
+__global__ void k_dig_commit(DigGeom g, DigWork w, DigCtl* ctl) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= (int64_t)NV * g.nt || stopped(ctl) || (ctl && ctl->failed2)) return;
+    if (e == 0 && ctl) ctl->iters += 1;
+    if (!idle_cell(g, (int)(e / NV))) w.prim[e] = w.next[e];
 }
 
 template <int NV>
@@ -1093,7 +1291,7 @@ __global__ void k_dig_closure_prep(DigGeom g, DigWork w) {
     const double lam = kn * dc;
     const double cs = sqrt(g.R * T);
     const double p = rho * g.R * T;
-    const double* gr = w.grad + 15 * (size_t)c;
+    const double* gr = w.rec + 20 * (size_t)c + 5;
     for (int k = 0; k < 9; ++k) x[k] = (float)(lam * gr[3 + k] / cs);
     for (int k = 0; k < 3; ++k) x[9 + k] = (float)(lam * gr[12 + k] / T);
     x[12] = (float)kn;
@@ -1171,8 +1369,8 @@ void launch_dig_kn(hipStream_t s, const DigGeom& g, DigWork w, double kn_ref, do
     hipLaunchKernelGGL(DIG_NV(g, k_dig_kn), cells_grid(g.nt), dim3(kDigThreads), 0, s, g, w, kn_ref, T0, rho0, L0);
 }
 
-void launch_dig_gradients(hipStream_t s, const DigGeom& g, const double* prim, double* grad, const DigCtl* ctl) {
-    hipLaunchKernelGGL(DIG_NV(g, k_dig_grad), cells_grid(4 * (int64_t)g.nt), dim3(kDigThreads), 0, s, g, prim, grad,
+void launch_dig_gradients(hipStream_t s, const DigGeom& g, const double* prim, double* rec, const DigCtl* ctl) {
+    hipLaunchKernelGGL(DIG_NV(g, k_dig_grad), cells_grid(4 * (int64_t)g.nt), dim3(kDigThreads), 0, s, g, prim, rec,
                        ctl);
 }
 
@@ -1199,35 +1397,52 @@ void launch_dig_copy(hipStream_t s, const double* src, double* dst, int64_t n) {
     hipLaunchKernelGGL(k_dig_copy, cells_grid(n), dim3(kDigThreads), 0, s, src, dst, n);
 }
 
-void launch_dig_residual(hipStream_t s, const DigGeom& g, const double* prim, const double* hotf, const double* grad,
-                         double* Rs, DigWork w, int first, double cfl) {
-    hipLaunchKernelGGL(DIG_NV(g, k_dig_residual), cells_grid(4 * (int64_t)g.nt), dim3(kDigThreads), 0, s, g, prim,
-                       hotf, grad, Rs, w, first, cfl);
+template <bool UPDATE>
+void run_residual(hipStream_t s, const DigGeom& g, const DigWork& w, const double* hotf, double* Rs, bool first, double cfl,
+                  const double* base, double* out, double alpha) {
+    const auto k = g.dr ? (first ? k_dig_residual<kDigNVR, UPDATE, true> : k_dig_residual<kDigNVR, UPDATE, false>)
+                        : (first ? k_dig_residual<kDigNV, UPDATE, true> : k_dig_residual<kDigNV, UPDATE, false>);
+    hipLaunchKernelGGL(k, cells_grid(4 * (int64_t)g.nt), dim3(kDigThreads), 0, s, g, (const double*)w.rec, hotf, Rs, w,
+                       cfl, base, out, alpha);
 }
 
-void launch_dig_face_hot(hipStream_t s, const DigGeom& g, const double* prim, const double* grad, const double* hot,
-                         double* hotf, int consistent) {
-    hipLaunchKernelGGL(DIG_NV(g, k_dig_face_hot), cells_grid(g.nt), dim3(kDigThreads), 0, s, g, prim, grad, hot, hotf,
-                       consistent);
+void launch_dig_residual(hipStream_t s, const DigGeom& g, const double* hotf, double* Rs, DigWork w, int first,
+                         double cfl) {
+    run_residual<false>(s, g, w, hotf, Rs, first != 0, cfl, nullptr, nullptr, 0.0);
 }
 
-// One pseudo-time iteration: three stages with weights 1/3, 1/2, 1; the
-// convergence test and the step size come from the first stage.
-void launch_dig_iteration(hipStream_t s, const DigGeom& g, DigWork w, double cfl, double eps_m, int global_dt,
-                          int it) {
+void launch_dig_face_hot(hipStream_t s, const DigGeom& g, const double* rec, const double* hot, double* hotf,
+                         int consistent) {
+    hipLaunchKernelGGL(DIG_NV(g, k_dig_face_hot), cells_grid(4 * (int64_t)g.nt), dim3(kDigThreads), 0, s, g, rec, hot,
+                       hotf, consistent);
+}
+
+// One pseudo-time iteration from `base` to `out`: three stages with weights
+// 1/3, 1/2, 1 (the residual reads records, so a stage may write where its
+// state came from); the convergence test and the step size come from the
+// first stage.
+void launch_dig_iteration(hipStream_t s, const DigGeom& g, DigWork w, const double* base, double* out, double cfl,
+                          double eps_m, int global_dt, int it) {
     const dim3 gr = cells_grid(g.nt), grq = cells_grid(4 * (int64_t)g.nt), bl(kDigThreads);
     const int nblk = (int)grq.x;  // partials of the residual kernel
     const double alpha[3] = {1.0 / 3.0, 0.5, 1.0};
-    hipLaunchKernelGGL(DIG_NV(g, k_dig_save), gr, bl, 0, s, g, w);
+    const double* in = base;
     for (int k = 0; k < 3; ++k) {
-        hipLaunchKernelGGL(DIG_NV(g, k_dig_grad), grq, bl, 0, s, g, (const double*)w.stage, w.grad,
-                           (const DigCtl*)w.ctl);
-        hipLaunchKernelGGL(DIG_NV(g, k_dig_residual), grq, bl, 0, s, g, (const double*)w.stage,
-                           (const double*)w.hotf, (const double*)w.grad, w.Rs, w, k == 0 ? 1 : 0, cfl);
+        double* to = k < 2 ? w.stage : out;
+        launch_dig_gradients(s, g, in, w.rec, w.ctl);
+        if (global_dt)
+            launch_dig_residual(s, g, w.hotf, w.Rs, w, k == 0, cfl);
+        else
+            run_residual<true>(s, g, w, w.hotf, nullptr, k == 0, cfl, base, to, alpha[k]);
         if (k == 0) hipLaunchKernelGGL(k_dig_check, dim3(1), bl, 0, s, w, nblk, it, eps_m);
-        hipLaunchKernelGGL(DIG_NV(g, k_dig_update), gr, bl, 0, s, g, w, alpha[k], global_dt);
+        if (global_dt) hipLaunchKernelGGL(DIG_NV(g, k_dig_update), gr, bl, 0, s, g, w, alpha[k], base, to);
+        in = to;
     }
-    hipLaunchKernelGGL(DIG_NV(g, k_dig_commit), gr, bl, 0, s, g, w);
+}
+
+void launch_dig_commit(hipStream_t s, const DigGeom& g, DigWork w, DigCtl* ctl) {
+    const int64_t n = (int64_t)(g.dr ? kDigNVR : kDigNV) * g.nt;
+    hipLaunchKernelGGL(DIG_NV(g, k_dig_commit), cells_grid(n), dim3(kDigThreads), 0, s, g, w, ctl);
 }
 
 // ---------------------------------------------------------------------------
@@ -1673,9 +1888,8 @@ __global__ void k_nk_commit(DigGeom g, DigWork w, NkWork nk) {
 
 void launch_nk_begin(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, NkScale sc, int it, double eps_m) {
     const dim3 gr = cells_grid(g.nt), grq = cells_grid(4 * (int64_t)g.nt), bl(kDigThreads);
-    hipLaunchKernelGGL(DIG_NV(g, k_dig_grad), grq, bl, 0, s, g, (const double*)w.prim, w.grad, (const DigCtl*)nullptr);
-    hipLaunchKernelGGL(DIG_NV(g, k_dig_residual), grq, bl, 0, s, g, (const double*)w.prim, (const double*)w.hotf,
-                       (const double*)w.grad, w.Rs, w, 1, 1.0);
+    launch_dig_gradients(s, g, w.prim, w.rec, nullptr);
+    launch_dig_residual(s, g, w.hotf, w.Rs, w, 1, 1.0);
     hipLaunchKernelGGL(k_dig_check, dim3(1), bl, 0, s, w, (int)grq.x, it, eps_m);
     hipLaunchKernelGGL(DIG_NV(g, k_nk_start), gr, bl, 0, s, g, w, nk, sc, it == 0 ? 1 : 0);
     hipLaunchKernelGGL(k_nk_reduce, dim3(2), bl, 0, s, (const double*)nk.part, (int)gr.x, nk.red + kNkBeta2(nk.m));
@@ -1690,13 +1904,11 @@ void launch_nk_scale(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, doub
 
 void launch_nk_arnoldi(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, NkScale sc, int j, double cfl,
                        double fd) {
-    const dim3 gr = cells_grid(g.nt), grq = cells_grid(4 * (int64_t)g.nt), bl(kDigThreads);
+    const dim3 gr = cells_grid(g.nt), bl(kDigThreads);
     const int nblk = (int)gr.x, m = nk.m;
     hipLaunchKernelGGL(DIG_NV(g, k_nk_perturb), gr, bl, 0, s, g, w, nk, sc, j, cfl);
-    hipLaunchKernelGGL(DIG_NV(g, k_dig_grad), grq, bl, 0, s, g, (const double*)w.stage, w.grad,
-                       (const DigCtl*)nullptr);
-    hipLaunchKernelGGL(DIG_NV(g, k_dig_residual), grq, bl, 0, s, g, (const double*)w.stage, (const double*)w.hotf,
-                       (const double*)w.grad, nk.Rp, w, 0, 1.0);
+    launch_dig_gradients(s, g, w.stage, w.rec, nullptr);
+    launch_dig_residual(s, g, w.hotf, nk.Rp, w, 0, 1.0);
     hipLaunchKernelGGL(DIG_NV(g, k_nk_matvec), gr, bl, 0, s, g, w, nk, sc, j, cfl);
     hipLaunchKernelGGL(k_nk_reduce, dim3(j + 1), bl, 0, s, (const double*)nk.part, nblk, nk.red + kNkH1(m));
     hipLaunchKernelGGL(DIG_NV(g, k_nk_orth), gr, bl, 0, s, g, nk, j, kNkH1(m), 0);

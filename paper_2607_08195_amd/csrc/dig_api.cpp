@@ -56,6 +56,7 @@ void build_geometry(const HostMesh& m, const std::vector<dsmc_boundary_desc>& bc
     G.lsq.assign(9 * (size_t)nt, 0.0);
     G.flink.assign(4 * (size_t)nt, 0);
     const double* X = m.xyz.data();
+    const size_t nf = 4 * (size_t)nt;  // face vectors are stored component by component
     for (int c = 0; c < nt; ++c) {
         const int32_t* q = &m.tv[4 * (size_t)c];
         for (int i = 0; i < 3; ++i) {
@@ -68,11 +69,11 @@ void build_geometry(const HostMesh& m, const std::vector<dsmc_boundary_desc>& bc
             for (int k = 0; k < 4; ++k)
                 if (k != f) v[j++] = q[k];
             for (int i = 0; i < 3; ++i)
-                G.fcen[12 * (size_t)c + 3 * f + i] =
+                G.fcen[i * nf + 4 * (size_t)c + f] =
                     ((X[3 * (size_t)v[0] + i] + X[3 * (size_t)v[1] + i]) + X[3 * (size_t)v[2] + i]) / 3.0;
             const double* pl = &m.plane[16 * (size_t)c + 4 * f];
             const double nn = std::sqrt(pl[0] * pl[0] + pl[1] * pl[1] + pl[2] * pl[2]);
-            for (int i = 0; i < 3; ++i) G.fnu[12 * (size_t)c + 3 * f + i] = pl[i] / nn;
+            for (int i = 0; i < 3; ++i) G.fnu[i * nf + 4 * (size_t)c + f] = pl[i] / nn;
             G.farea[4 * (size_t)c + f] = 0.5 * nn;
         }
     }
@@ -80,8 +81,9 @@ void build_geometry(const HostMesh& m, const std::vector<dsmc_boundary_desc>& bc
         const double* xc = &G.cen[3 * (size_t)c];
         for (int f = 0; f < 4; ++f) {
             const int code = m.nbr[4 * (size_t)c + f];
-            double* dx = &G.fdx[12 * (size_t)c + 3 * f];
-            const double* xf = &G.fcen[12 * (size_t)c + 3 * f];
+            const size_t t = 4 * (size_t)c + f;
+            double dx[3];
+            const double xf[3] = {G.fcen[t], G.fcen[nf + t], G.fcen[2 * nf + t]};
             int32_t link;
             if (code >= 0) {
                 const int nb = code >> 2;
@@ -104,13 +106,15 @@ void build_geometry(const HostMesh& m, const std::vector<dsmc_boundary_desc>& bc
                     link = kind | (grp << 3);
                 }
             }
-            G.flink[4 * (size_t)c + f] = link;
+            G.flink[t] = link;
+            for (int i = 0; i < 3; ++i) G.fdx[i * nf + t] = dx[i];
         }
         double A[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
         for (int f = 0; f < 4; ++f) {
             const int kind = G.flink[4 * (size_t)c + f] & 7;
             if (kind != kLinkInterior && kind != kLinkPeriodic && kind != kLinkWall) continue;
-            const double* dx = &G.fdx[12 * (size_t)c + 3 * f];
+            const size_t t = 4 * (size_t)c + f;
+            const double dx[3] = {G.fdx[t], G.fdx[nf + t], G.fdx[2 * nf + t]};
             const double w = 1.0 / (dx[0] * dx[0] + dx[1] * dx[1] + dx[2] * dx[2]);
             for (int i = 0; i < 3; ++i)
                 for (int j = 0; j < 3; ++j) A[i][j] += w * dx[i] * dx[j];
@@ -171,10 +175,10 @@ dsmc_status ensure(dsmc_ctx c) {
               alloc_n(c, flink, G.flink.size()) && alloc_n(c, groups, ng + 1);
     ok = ok && alloc_n(c, w.samp, ns * nt) && alloc_n(c, w.ok, nt) && alloc_n(c, w.prim, nv * nt) &&
          alloc_n(c, w.half, nv * nt) && alloc_n(c, w.hot, nh * nt) && alloc_n(c, w.hotf, 4 * nh * nt) &&
-         alloc_n(c, w.grad, 3 * nv * nt) && alloc_n(c, w.kn, nt) && alloc_n(c, w.avail, nt) &&
+         alloc_n(c, w.rec, 4 * nv * nt) && alloc_n(c, w.kn, nt) && alloc_n(c, w.avail, nt) &&
          alloc_n(c, w.navail, nt) && alloc_n(c, w.nprim, nv * nt) && alloc_n(c, w.nhot, nh * nt) &&
          alloc_n(c, w.state, nt) && alloc_n(c, w.mprev, nv * nt) && alloc_n(c, w.Rs, nv * nt) &&
-         alloc_n(c, w.dt, nt) && alloc_n(c, w.U0, nv * nt) && alloc_n(c, w.stage, nv * nt) &&
+         alloc_n(c, w.dt, nt) && alloc_n(c, w.next, nv * nt) && alloc_n(c, w.stage, nv * nt) &&
          alloc_n(c, w.partial, 8 * (size_t)d->nblk) && alloc_n(c, w.ctl, 1) && alloc_n(c, w.fb_cnt, nt) &&
          alloc_n(c, w.fb_off, nt + 1) && alloc_n(c, w.fb_tgt, nt) && alloc_n(c, w.cx, 13 * (size_t)nt) &&
          alloc_n(c, w.ct, 9 * (size_t)nt) && alloc_n(c, w.cs, 9 * (size_t)nt) && alloc_n(c, w.cy, 9 * (size_t)nt) &&
@@ -282,9 +286,11 @@ dsmc_status ensure(dsmc_ctx c) {
     g.groups = groups;
     g.mass = c->mass;
     g.R = kBoltzmann / c->mass;
+    g.cv = Divisor(1.5 * g.R);
     g.mu_ref = mu_ref_of(c);
     g.omega = c->omega;
-    g.T_ref = c->Tref;
+    g.T_ref = Divisor(c->Tref);
+    g.mass4 = Divisor(4.0 * c->mass);
     g.FN = c->FN;
     g.cell_case = ncase ? c->d_cell_case : nullptr;
     g.n_cases = ncase;
@@ -320,6 +326,7 @@ DigCtl read_ctl(dsmc_ctx c, dsmc_status* st) {
         c->broken = true;
         *st = fail(c, DSMC_E_DEVICE, "reading the coupling control block failed");
     }
+    h.failed |= h.failed2;
     return h;
 }
 
@@ -414,7 +421,8 @@ dsmc_status run_solve_aa(dsmc_ctx c, const dig_params* p, dig_report* r, int m) 
     for (int it = 0; it < p->n_m; ++it) {
         const int par = it & 1;
         HIP_TRY(c, hipMemcpyAsync(a.x, d->w.prim, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-        launch_dig_iteration(s, d->g, d->w, p->cfl, p->eps_m, p->global_dt ? 1 : 0, it);
+        launch_dig_iteration(s, d->g, d->w, d->w.prim, d->w.next, p->cfl, p->eps_m, p->global_dt ? 1 : 0, it);
+        launch_dig_commit(s, d->g, d->w, d->w.ctl);
         const int slot = fresh ? 0 : made % m;
         launch_aa_diff(s, d->g, a, d->w.prim, slot, fresh ? 1 : 0, par);
         const int ncnt = fresh ? 0 : std::min(cnt + 1, m);
@@ -423,6 +431,7 @@ dsmc_status run_solve_aa(dsmc_ctx c, const dig_params* p, dig_report* r, int m) 
         HIP_TRY(c, hipMemcpyAsync(&h, d->w.ctl, sizeof h, hipMemcpyDeviceToHost, s));
         HIP_TRY(c, hipStreamSynchronize(s));
         HIP_TRY(c, hipGetLastError());
+        h.failed |= h.failed2;
         if (h.conv || h.failed) break;
         if (fresh) {
             fresh = false;
@@ -625,8 +634,13 @@ dsmc_status run_solve(dsmc_ctx c, const dig_params* p, dig_report* r) {
     launch_dig_ctl_reset(c->stream, d->w.ctl);
     dsmc_status st = DSMC_OK;
     DigCtl h{};
+    int run = 0;
     for (int it = 0; it < p->n_m; ++it) {
-        launch_dig_iteration(c->stream, d->g, d->w, p->cfl, p->eps_m, p->global_dt ? 1 : 0, it);
+        // the state goes back and forth between two arrays, so that an
+        // iteration that stops leaves the one it began from
+        launch_dig_iteration(c->stream, d->g, d->w, it & 1 ? d->w.next : d->w.prim, it & 1 ? d->w.prim : d->w.next,
+                             p->cfl, p->eps_m, p->global_dt ? 1 : 0, it);
+        ++run;
         if ((it + 1) % kPollEvery == 0 && it + 1 < p->n_m) {
             HIP_TRY(c, hipGetLastError());
             h = read_ctl(c, &st);
@@ -637,7 +651,11 @@ dsmc_status run_solve(dsmc_ctx c, const dig_params* p, dig_report* r) {
     HIP_TRY(c, hipGetLastError());
     h = read_ctl(c, &st);
     if (st != DSMC_OK) return st;
-    r->iters = h.iters;
+    r->iters = h.conv || h.failed ? h.iters : run;
+    if (r->iters & 1) {
+        launch_dig_commit(c->stream, d->g, d->w, nullptr);
+        HIP_TRY(c, hipGetLastError());
+    }
     r->residual = h.res0 > 0 ? h.res / h.res0 : 0.0;
     r->converged = h.conv;
     r->failed = h.failed;
@@ -743,7 +761,7 @@ dsmc_status dig_couple(dsmc_ctx c, const dig_params* p, dig_report* rep) {
     launch_dig_ctl_reset(s, d->w.ctl);
     launch_dig_sampled(s, d->g, c->d_ewma, c->dr ? c->d_rewma : nullptr, c->FN, d->w);
     launch_dig_kn(s, d->g, d->w, kn_ref, T0, rho0, p->L0);
-    launch_dig_gradients(s, d->g, d->w.prim, d->w.grad, nullptr);
+    launch_dig_gradients(s, d->g, d->w.prim, d->w.rec, nullptr);
     launch_dig_hot(s, d->g, d->w);
     launch_dig_closure_prep(s, d->g, d->w);
     if (c->closure) {
@@ -753,8 +771,8 @@ dsmc_status dig_couple(dsmc_ctx c, const dig_params* p, dig_report* rep) {
     launch_dig_gate(s, d->g, d->w, p->kn_max, p->passes);
     launch_dig_copy(s, d->w.prim, d->w.half, nv * (int64_t)nt);
     // the solve's face HoT, consistent with M^{k+1/2}
-    launch_dig_gradients(s, d->g, d->w.half, d->w.grad, nullptr);
-    launch_dig_face_hot(s, d->g, d->w.half, d->w.grad, d->w.hot, d->w.hotf, 1);
+    launch_dig_gradients(s, d->g, d->w.half, d->w.rec, nullptr);
+    launch_dig_face_hot(s, d->g, d->w.rec, d->w.hot, d->w.hotf, 1);
     if (p->warm_start) launch_dig_copy(s, d->w.mprev, d->w.prim, nv * (int64_t)nt);
     HIP_TRY(c, hipGetLastError());
     DigCtl h = read_ctl(c, &st);
@@ -816,9 +834,9 @@ dsmc_status dig_residual(dsmc_ctx c, const double* prim, const double* hot, doub
     if ((st = to_device(c, d->w.stage, prim, dig_nv(c))) != DSMC_OK) return st;
     if ((st = to_device(c, d->w.nhot, hot, dig_nh(c))) != DSMC_OK) return st;
     launch_dig_ctl_reset(c->stream, d->w.ctl);
-    launch_dig_gradients(c->stream, d->g, d->w.stage, d->w.grad, d->w.ctl);
-    launch_dig_face_hot(c->stream, d->g, d->w.stage, d->w.grad, d->w.nhot, d->w.hotf, 0);
-    launch_dig_residual(c->stream, d->g, d->w.stage, d->w.hotf, d->w.grad, d->w.Rs, d->w, 0, 1.0);
+    launch_dig_gradients(c->stream, d->g, d->w.stage, d->w.rec, d->w.ctl);
+    launch_dig_face_hot(c->stream, d->g, d->w.rec, d->w.nhot, d->w.hotf, 0);
+    launch_dig_residual(c->stream, d->g, d->w.hotf, d->w.Rs, d->w, 0, 1.0);
     HIP_TRY(c, hipGetLastError());
     return to_host(c, out, d->w.Rs, dig_nv(c));
 }
@@ -832,8 +850,8 @@ dsmc_status dig_solve(dsmc_ctx c, double* prim, const double* hot, const dig_par
     DigState* d = c->dig;
     if ((st = to_device(c, d->w.prim, (const double*)prim, dig_nv(c))) != DSMC_OK) return st;
     if ((st = to_device(c, d->w.hot, hot, dig_nh(c))) != DSMC_OK) return st;
-    launch_dig_gradients(c->stream, d->g, d->w.prim, d->w.grad, nullptr);
-    launch_dig_face_hot(c->stream, d->g, d->w.prim, d->w.grad, d->w.hot, d->w.hotf, 0);
+    launch_dig_gradients(c->stream, d->g, d->w.prim, d->w.rec, nullptr);
+    launch_dig_face_hot(c->stream, d->g, d->w.rec, d->w.hot, d->w.hotf, 0);
     dig_report r{};
     if ((st = run_solve(c, p, &r)) != DSMC_OK) return st;
     if ((st = to_host(c, prim, d->w.prim, dig_nv(c))) != DSMC_OK) return st;

@@ -92,6 +92,7 @@ struct DigCtl {
     double res0, res, dtmin;
     int conv, failed, iters;
     int failed1, failed2;  // found by an iteration's first stage and by its later ones
+    int halt;              // Newton-Krylov: what was launched ahead is left out
     int n_rejected, n_reconstructed, n_unreached;
     int n_closure, n_fallback;
     double mass_scale;
@@ -208,9 +209,12 @@ struct NkWork {
     double* Ut;    // [nt][NV] trial state
     double* R0;    // [nt][NV] residual at U
     double* Rp;    // [nt][NV] residual at the perturbed state
-    double* part;  // [m + 1][blocks] block partials
+    double* part;  // [m + 2][blocks] block partials (the last column: k_nk_normalize's)
     double* red;   // reduced values, slots below
     double* y;     // [m] coefficients of the update
+    double* gm;    // Hessenberg columns under the rotations, rotations, right-hand side, offsets below
+    double* host;  // pinned: slot 0 of a Newton step's start, then kNkAhead of GMRES steps
+    hipEvent_t ev[2];  // GMRES step done
     int32_t* flag; // a trial or perturbed cell was not physical
     int m;
 };
@@ -225,21 +229,33 @@ __host__ __device__ constexpr int kNkEps(int m) { return 2 * m + 4; }
 __host__ __device__ constexpr int kNkBeta2(int m) { return 2 * m + 5; }
 __host__ __device__ constexpr int kNkXr2(int m) { return 2 * m + 6; }
 __host__ __device__ constexpr int kNkRedSize(int m) { return 2 * m + 7; }
+__host__ __device__ constexpr int kNkCs(int m) { return m * (m + 1); }
+__host__ __device__ constexpr int kNkSn(int m) { return m * (m + 2); }
+__host__ __device__ constexpr int kNkGv(int m) { return m * (m + 3); }
+__host__ __device__ constexpr int kNkGmSize(int m) { return m * (m + 4) + 1; }
+constexpr int kNkAhead = 2;     // GMRES steps in the stream at a time
+constexpr int kNkHostSlot = 4;  // doubles
 // Residual and spectral sums at w.prim (w.Rs, w.dt = V / S), the stopping
 // test of Newton step `it` (w.ctl), R0, U (from w.prim when it == 0), V_0 =
-// -R0 / scale; |V_0|^2 and |U/scale|^2 into red.
+// -R0 / scale; |V_0|^2 and |U/scale|^2 into red; then the report.
 void launch_nk_begin(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, NkScale sc, int it, double eps_m);
+// Host slot 0: 0 going on, 1 converged, 2 halted (the trial state was not
+// physical); |V_0|^2, res, res0.
+void launch_nk_report(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk);
 // V_0 /= sqrt(red[beta2]) and the finite-difference step of its product.
 void launch_nk_scale(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, double cfl, double fd);
-// Arnoldi step j: the product with V_j, two Gram-Schmidt passes (H column j
-// = red[H1] + red[H2], |w|^2 in red[Hn2]), V_{j+1} and the next step.
-void launch_nk_arnoldi(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, NkScale sc, int j, double cfl,
-                       double fd);
-// Trial state U + alpha P^-1 V y (y in nk.y, jn terms) into nk.Ut, w.stage.
+// GMRES step j: the product with V_j, two Gram-Schmidt passes, V_{j+1}, the
+// next finite-difference step, the rotation; host slot 1 + j % kNkAhead: 0
+// going on, 1 the cycle ends here, 2 a perturbed cell was not physical; the
+// linear residual over its start.
+void launch_nk_arnoldi(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, NkScale sc, int j, double cfl, double fd,
+                       double eta);
+// The update's coefficients after jn steps into nk.y; no flag, no halt.
+void launch_nk_solve(hipStream_t s, DigWork w, NkWork nk, int jn);
+// Trial state U + alpha P^-1 V y; where every cell of it is physical it
+// becomes U and w.prim, else what follows is halted.
 void launch_nk_try(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, NkScale sc, int jn, double alpha,
                    double cfl);
-// U = Ut, w.prim = w.stage.
-void launch_nk_commit(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk);
 
 // Local-accumulation flags from the gate states (cases of a batch that are
 // not coupled keep theirs).

@@ -31,7 +31,9 @@ template <int NV> struct Widths {
     static constexpr int NG = 3 * NV;
 };
 
-__device__ __forceinline__ bool stopped(const DigCtl* ctl) { return ctl != nullptr && (ctl->conv | ctl->failed); }
+__device__ __forceinline__ bool stopped(const DigCtl* ctl) {
+    return ctl != nullptr && (ctl->conv | ctl->failed | ctl->halt);
+}
 
 __device__ __forceinline__ double mu_of(const DigGeom& g, double T) { return g.mu_ref * pow(g.T_ref.of(T), g.omega); }
 __device__ __forceinline__ double kappa_of(const DigGeom& g, double mu) {
@@ -707,6 +709,7 @@ __global__ void k_dig_ctl_reset(DigCtl* ctl) {
     ctl->failed = 0;
     ctl->failed1 = 0;
     ctl->failed2 = 0;
+    ctl->halt = 0;
     ctl->iters = 0;
     ctl->n_rejected = 0;
     ctl->n_reconstructed = 0;
@@ -1561,8 +1564,16 @@ void launch_aa_update(hipStream_t s, const DigGeom& g, const AaWork& a, int cnt,
 // NkScale; the right preconditioner divides cell c's unknowns by
 // p_c = S_c (1 + 1/cfl), S_c = V_c / dt_c the sum that sets the marching's
 // local step (the residual kernel's dt at CFL number 1).  Inner products are
-// reduced in a fixed order: wave, then the block's four waves, then
-// k_nk_reduce over the blocks.
+// reduced in a fixed order: wave, then the block's four waves, then over the
+// blocks: k_nk_reduce for the many columns of a Gram-Schmidt pass, the next
+// kernel's own blocks for one or two (nk_fold; for many it measured 107 us a
+// GMRES step against 98 on 63,888 cells, and no gain on 6,000).
+//
+// The device carries the GMRES cycle by itself (k_nk_step: rotations, residual,
+// stop), so that the host launches ahead of it: with a host round trip per
+// GMRES step the GPU was idle for half of the solve (20,250 cells of nitrogen,
+// a coupling step of 6 Newton steps and 5 particle steps: 13.3 -> 8.5 ms).  A cycle that has come to
+// its end halts what was launched beyond it (ctl->halt).
 
 // Per-column block partials: column i's value of this lane is added over the
 // block and written to part[i * nblk + block].
@@ -1617,7 +1628,8 @@ __device__ __forceinline__ void nk_block_dots(double (*red)[kDigThreads / 64], c
 }
 
 // Fixed-order sum over the blocks of column blockIdx.x into out[blockIdx.x].
-__global__ __launch_bounds__(kDigThreads) void k_nk_reduce(const double* part, int nblk, double* out) {
+__global__ __launch_bounds__(kDigThreads) void k_nk_reduce(const DigCtl* ctl, const double* part, int nblk, double* out) {
+    if (stopped(ctl)) return;
     const double* p = part + (size_t)blockIdx.x * nblk;
     double s = 0.0;
     for (int b = threadIdx.x; b < nblk; b += kDigThreads) s += p[b];
@@ -1627,10 +1639,28 @@ __global__ __launch_bounds__(kDigThreads) void k_nk_reduce(const double* part, i
     if (threadIdx.x == 0) out[blockIdx.x] = tot;
 }
 
-// The finite-difference step of the next product from the reduced
-// sum of squares of the preconditioned direction and that of the state.
-__global__ __launch_bounds__(kDigThreads) void k_nk_reduce_eps(const double* part, int nblk, double* red, int m,
-                                                                double n, double fd) {
+// The same sums of columns 0..ncol-1 into LDS, a wave per column, in the order
+// of k_nk_reduce; ends with a barrier.
+__device__ __forceinline__ void nk_fold(const double* part, int nblk, int ncol, double* out) {
+    const int lane = threadIdx.x & 63;
+    for (int i = threadIdx.x >> 6; i < ncol; i += kDigThreads / 64) {
+        const double* p = part + (size_t)i * nblk;
+        double q[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int b = lane; b < nblk; b += kDigThreads)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (b + 64 * k < nblk) q[k] += p[b + 64 * k];
+        double s = (q[0] + q[2]) + (q[1] + q[3]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+        if (lane == 0) out[i] = s;
+    }
+    __syncthreads();
+}
+
+// The finite-difference step of the next product from the sum of squares of
+// the preconditioned direction (its block partials) and that of the state.
+__device__ __forceinline__ void nk_eps(const double* part, int nblk, double* red, int m, double n, double fd) {
     double s = 0.0;
     for (int b = threadIdx.x; b < nblk; b += kDigThreads) s += part[b];
     __shared__ double tot, dummy;
@@ -1643,11 +1673,88 @@ __global__ __launch_bounds__(kDigThreads) void k_nk_reduce_eps(const double* par
     }
 }
 
+// Start of a GMRES cycle: the first finite-difference step.
+__global__ __launch_bounds__(kDigThreads) void k_nk_reduce_eps(const double* part, int nblk, double* red, int m,
+                                                                double n, double fd) {
+    nk_eps(part, nblk, red, m, n, fd);
+}
+
+// End of GMRES step j (one workgroup): the next finite-difference step; the
+// Hessenberg column under the rotations so far, the new rotation, the linear
+// residual.  The cycle ends where that is at most eta of its start, where
+// the basis is complete, or where a perturbed cell was not physical.
+__global__ __launch_bounds__(kDigThreads) void k_nk_step(const double* part, int nblk, NkWork nk, DigCtl* ctl, int j,
+                                                         double n, double fd, double eta, double* host) {
+    if (stopped(ctl)) return;
+    const int m = nk.m, t = threadIdx.x;
+    __shared__ double h[kNkMaxKrylov + 2], cs[kNkMaxKrylov], sn[kNkMaxKrylov];
+    if (t <= j) h[t] = (0.0 + nk.red[kNkH1(m) + t]) + nk.red[kNkH2(m) + t];
+    if (t < j) {
+        cs[t] = nk.gm[kNkCs(m) + t];
+        sn[t] = nk.gm[kNkSn(m) + t];
+    }
+    nk_eps(part, nblk, nk.red, m, n, fd);  // (its barriers order the loads above)
+    if (t != 0) return;
+    const double beta = sqrt(nk.red[kNkBeta2(m)]), hn = sqrt(nk.red[kNkHn2(m)]);
+    double* H = nk.gm + (size_t)j * (m + 1);  // column j
+    double a = h[0];
+    for (int i = 0; i < j; ++i) {
+        const double b = h[i + 1];
+        H[i] = cs[i] * a + sn[i] * b;
+        a = -sn[i] * a + cs[i] * b;
+    }
+    const double b = hn, rr = sqrt(a * a + b * b);
+    const double c = rr > 0 ? a / rr : 1.0, s = rr > 0 ? b / rr : 0.0;
+    H[j] = rr;
+    nk.gm[kNkCs(m) + j] = c;
+    nk.gm[kNkSn(m) + j] = s;
+    double* gv = nk.gm + kNkGv(m);
+    const double g0 = j == 0 ? beta : gv[j];
+    const double g1 = -s * g0;
+    gv[j + 1] = g1;
+    gv[j] = c * g0;
+    const int stop = *nk.flag ? 2 : fabs(g1) <= eta * beta || !(hn > 0) ? 1 : 0;
+    if (stop) ctl->halt = 1;
+    volatile double* out = host;
+    out[0] = stop;
+    out[1] = fabs(g1) / beta;
+    __threadfence_system();
+}
+
+// End of a GMRES cycle of jn steps (one workgroup): the update's coefficients
+// by back substitution, each row's terms taken off in ascending order.
+__global__ __launch_bounds__(kDigThreads) void k_nk_solve(NkWork nk, DigCtl* ctl, int jn) {
+    __shared__ double H[kNkMaxKrylov * (kNkMaxKrylov + 1) / 2], y[kNkMaxKrylov], p[kNkMaxKrylov],
+        gv[kNkMaxKrylov];
+    const int m = nk.m, t = threadIdx.x;
+    if (t < jn) gv[t] = nk.gm[kNkGv(m) + t];
+    for (int e = t; e < jn * jn; e += kDigThreads) {
+        const int i = e % jn, l = e / jn;
+        if (i <= l) H[l * (l + 1) / 2 + i] = nk.gm[(size_t)l * (m + 1) + i];
+    }
+    for (int i = jn - 1; i >= 0; --i) {
+        __syncthreads();
+        for (int l = i + 1 + t; l < jn; l += kDigThreads) p[l] = H[l * (l + 1) / 2 + i] * y[l];
+        __syncthreads();
+        if (t == 0) {
+            double r = gv[i];
+            for (int l = i + 1; l < jn; ++l) r -= p[l];
+            y[i] = r / H[i * (i + 1) / 2 + i];
+            nk.y[i] = y[i];
+        }
+    }
+    if (t == 0) {
+        *nk.flag = 0;
+        ctl->halt = 0;
+    }
+}
+
 // Start of a Newton step: R0 = the residual just computed; U from the
 // primitives on the first step; V_0 = -R0 / scale; partials of |V_0|^2 and
 // |U / scale|^2.
 template <int NV>
 __global__ __launch_bounds__(kDigThreads) void k_nk_start(DigGeom g, DigWork w, NkWork nk, NkScale sc, int first) {
+    if (w.ctl->halt) return;
     __shared__ double red[2][kDigThreads / 64];
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     double b2 = 0.0, x2 = 0.0;
@@ -1681,6 +1788,24 @@ __global__ __launch_bounds__(kDigThreads) void k_nk_start(DigGeom g, DigWork w, 
     nk_block_store(red, 2, nk.part);
 }
 
+// Sums of k_nk_start, and what the host decides by (one workgroup).
+__global__ __launch_bounds__(kDigThreads) void k_nk_started(NkWork nk, const DigCtl* ctl, int nblk, double* host) {
+    __shared__ double s[2];
+    const int halt = ctl->halt;
+    if (!halt) nk_fold(nk.part, nblk, 2, s);
+    if (threadIdx.x != 0) return;
+    volatile double* out = host;
+    out[0] = halt ? 2.0 : ctl->conv ? 1.0 : 0.0;
+    if (!halt) {
+        nk.red[kNkBeta2(nk.m)] = s[0];
+        nk.red[kNkXr2(nk.m)] = s[1];
+        out[1] = s[0];
+        out[2] = ctl->res;
+        out[3] = ctl->res0;
+    }
+    __threadfence_system();
+}
+
 // V_0 /= beta; partial of |V_0 / p|^2 (the next finite-difference step).
 template <int NV>
 __global__ __launch_bounds__(kDigThreads) void k_nk_scale(DigGeom g, DigWork w, NkWork nk, double cfl) {
@@ -1699,6 +1824,7 @@ __global__ __launch_bounds__(kDigThreads) void k_nk_scale(DigGeom g, DigWork w, 
             q2 += q * q;
         }
     }
+    if (blockIdx.x == 0 && threadIdx.x == 0) *nk.flag = 0;
     nk_block_column(red, 0, q2);
     nk_block_store(red, 1, nk.part);
 }
@@ -1709,7 +1835,7 @@ template <int NV>
 __global__ __launch_bounds__(kDigThreads) void k_nk_perturb(DigGeom g, DigWork w, NkWork nk, NkScale sc, int j,
                                                             double cfl) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= g.nt) return;
+    if (c >= g.nt || stopped(w.ctl)) return;
     const double eps = nk.red[kNkEps(nk.m)];
     const double pc = g.vol[c] / w.dt[c] * (1.0 + 1.0 / cfl);
     const double* vj = nk.V + (size_t)j * NV * g.nt;
@@ -1729,6 +1855,7 @@ __global__ __launch_bounds__(kDigThreads) void k_nk_perturb(DigGeom g, DigWork w
 template <int NV>
 __global__ __launch_bounds__(kDigThreads) void k_nk_matvec(DigGeom g, DigWork w, NkWork nk, NkScale sc, int j,
                                                            double cfl) {
+    if (stopped(w.ctl)) return;
     __shared__ double red[kNkMaxKrylov + 1][kDigThreads / 64];
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     const bool live = c < g.nt;
@@ -1756,7 +1883,9 @@ __global__ __launch_bounds__(kDigThreads) void k_nk_matvec(DigGeom g, DigWork w,
 // w -= sum_{i <= j} h_i V_i with h = red[off ...]; then partials of the next
 // pass's <V_i, w> (norm = 0) or of |w|^2 (norm = 1).
 template <int NV>
-__global__ __launch_bounds__(kDigThreads) void k_nk_orth(DigGeom g, NkWork nk, int j, int off, int norm) {
+__global__ __launch_bounds__(kDigThreads) void k_nk_orth(DigGeom g, const DigCtl* ctl, NkWork nk, int j, int off,
+                                                         int norm) {
+    if (stopped(ctl)) return;
     __shared__ double red[kNkMaxKrylov + 1][kDigThreads / 64];
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     const bool live = c < g.nt;
@@ -1807,13 +1936,18 @@ __global__ __launch_bounds__(kDigThreads) void k_nk_orth(DigGeom g, NkWork nk, i
     nk_block_store(red, j + 1, nk.part);
 }
 
-// V_{j+1} = w / |w| (when |w| > 0); partial of |V_{j+1} / p|^2.
+// V_{j+1} = w / |w| (when |w| > 0), |w|^2 from its block partials `in`;
+// partial of |V_{j+1} / p|^2 into `part`.
 template <int NV>
-__global__ __launch_bounds__(kDigThreads) void k_nk_normalize(DigGeom g, DigWork w, NkWork nk, int j, double cfl) {
-    __shared__ double red[1][kDigThreads / 64];
+__global__ __launch_bounds__(kDigThreads) void k_nk_normalize(DigGeom g, DigWork w, NkWork nk, int j, double cfl,
+                                                              const double* in, double* part) {
+    if (stopped(w.ctl)) return;
+    __shared__ double red[1][kDigThreads / 64], hn2;
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     double q2 = 0.0;
-    const double hn = sqrt(nk.red[kNkHn2(nk.m)]);
+    nk_fold(in, gridDim.x, 1, &hn2);
+    if (blockIdx.x == 0 && threadIdx.x == 0) nk.red[kNkHn2(nk.m)] = hn2;
+    const double hn = sqrt(hn2);
     if (c < g.nt && hn > 0) {
         const size_t n = (size_t)NV * g.nt;
         const double pc = g.vol[c] / w.dt[c] * (1.0 + 1.0 / cfl);
@@ -1827,7 +1961,7 @@ __global__ __launch_bounds__(kDigThreads) void k_nk_normalize(DigGeom g, DigWork
         }
     }
     nk_block_column(red, 0, q2);
-    nk_block_store(red, 1, nk.part);
+    nk_block_store(red, 1, part);
 }
 
 // Trial state U + alpha dU, dU the preconditioned sum_{i < jn} y_i V_i, into
@@ -1874,9 +2008,15 @@ __global__ __launch_bounds__(kDigThreads) void k_nk_try(DigGeom g, DigWork w, Nk
     for (int v = 0; v < NV; ++v) w.stage[NV * (size_t)c + v] = P[v];
 }
 
+// The trial state, if every cell of it is physical; if not, what follows is
+// halted and the host tries a shorter update.
 template <int NV>
 __global__ void k_nk_commit(DigGeom g, DigWork w, NkWork nk) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (*nk.flag) {
+        if (c == 0) w.ctl->halt = 1;
+        return;
+    }
     if (c >= g.nt) return;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
@@ -1888,11 +2028,16 @@ __global__ void k_nk_commit(DigGeom g, DigWork w, NkWork nk) {
 
 void launch_nk_begin(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, NkScale sc, int it, double eps_m) {
     const dim3 gr = cells_grid(g.nt), grq = cells_grid(4 * (int64_t)g.nt), bl(kDigThreads);
-    launch_dig_gradients(s, g, w.prim, w.rec, nullptr);
+    launch_dig_gradients(s, g, w.prim, w.rec, w.ctl);
     launch_dig_residual(s, g, w.hotf, w.Rs, w, 1, 1.0);
     hipLaunchKernelGGL(k_dig_check, dim3(1), bl, 0, s, w, (int)grq.x, it, eps_m);
     hipLaunchKernelGGL(DIG_NV(g, k_nk_start), gr, bl, 0, s, g, w, nk, sc, it == 0 ? 1 : 0);
-    hipLaunchKernelGGL(k_nk_reduce, dim3(2), bl, 0, s, (const double*)nk.part, (int)gr.x, nk.red + kNkBeta2(nk.m));
+    launch_nk_report(s, g, w, nk);
+}
+
+void launch_nk_report(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk) {
+    hipLaunchKernelGGL(k_nk_started, dim3(1), dim3(kDigThreads), 0, s, nk, (const DigCtl*)w.ctl, (int)cells_grid(g.nt).x,
+                       nk.host);
 }
 
 void launch_nk_scale(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, double cfl, double fd) {
@@ -1902,31 +2047,34 @@ void launch_nk_scale(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, doub
                        (double)(g.dr ? kDigNVR : kDigNV) * g.nt, fd);
 }
 
-void launch_nk_arnoldi(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, NkScale sc, int j, double cfl,
-                       double fd) {
+void launch_nk_arnoldi(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, NkScale sc, int j, double cfl, double fd,
+                       double eta) {
     const dim3 gr = cells_grid(g.nt), bl(kDigThreads);
     const int nblk = (int)gr.x, m = nk.m;
+    double *A = nk.part, *B = nk.part + (size_t)nblk * (m + 1);
+    const DigCtl* ctl = w.ctl;
     hipLaunchKernelGGL(DIG_NV(g, k_nk_perturb), gr, bl, 0, s, g, w, nk, sc, j, cfl);
-    launch_dig_gradients(s, g, w.stage, w.rec, nullptr);
+    launch_dig_gradients(s, g, w.stage, w.rec, w.ctl);
     launch_dig_residual(s, g, w.hotf, nk.Rp, w, 0, 1.0);
     hipLaunchKernelGGL(DIG_NV(g, k_nk_matvec), gr, bl, 0, s, g, w, nk, sc, j, cfl);
-    hipLaunchKernelGGL(k_nk_reduce, dim3(j + 1), bl, 0, s, (const double*)nk.part, nblk, nk.red + kNkH1(m));
-    hipLaunchKernelGGL(DIG_NV(g, k_nk_orth), gr, bl, 0, s, g, nk, j, kNkH1(m), 0);
-    hipLaunchKernelGGL(k_nk_reduce, dim3(j + 1), bl, 0, s, (const double*)nk.part, nblk, nk.red + kNkH2(m));
-    hipLaunchKernelGGL(DIG_NV(g, k_nk_orth), gr, bl, 0, s, g, nk, j, kNkH2(m), 1);
-    hipLaunchKernelGGL(k_nk_reduce, dim3(1), bl, 0, s, (const double*)nk.part, nblk, nk.red + kNkHn2(m));
-    hipLaunchKernelGGL(DIG_NV(g, k_nk_normalize), gr, bl, 0, s, g, w, nk, j, cfl);
-    hipLaunchKernelGGL(k_nk_reduce_eps, dim3(1), bl, 0, s, (const double*)nk.part, nblk, nk.red, m,
-                       (double)(g.dr ? kDigNVR : kDigNV) * g.nt, fd);
+    hipLaunchKernelGGL(k_nk_reduce, dim3(j + 1), bl, 0, s, ctl, (const double*)A, nblk, nk.red + kNkH1(m));
+    hipLaunchKernelGGL(DIG_NV(g, k_nk_orth), gr, bl, 0, s, g, ctl, nk, j, kNkH1(m), 0);
+    hipLaunchKernelGGL(k_nk_reduce, dim3(j + 1), bl, 0, s, ctl, (const double*)A, nblk, nk.red + kNkH2(m));
+    hipLaunchKernelGGL(DIG_NV(g, k_nk_orth), gr, bl, 0, s, g, ctl, nk, j, kNkH2(m), 1);
+    hipLaunchKernelGGL(DIG_NV(g, k_nk_normalize), gr, bl, 0, s, g, w, nk, j, cfl, (const double*)A, B);
+    hipLaunchKernelGGL(k_nk_step, dim3(1), bl, 0, s, (const double*)B, nblk, nk, w.ctl, j,
+                       (double)(g.dr ? kDigNVR : kDigNV) * g.nt, fd, eta, nk.host + kNkHostSlot * (1 + j % kNkAhead));
+}
+
+void launch_nk_solve(hipStream_t s, DigWork w, NkWork nk, int jn) {
+    hipLaunchKernelGGL(k_nk_solve, dim3(1), dim3(kDigThreads), 0, s, nk, w.ctl, jn);
 }
 
 void launch_nk_try(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, NkScale sc, int jn, double alpha,
                    double cfl) {
-    hipLaunchKernelGGL(DIG_NV(g, k_nk_try), cells_grid(g.nt), dim3(kDigThreads), 0, s, g, w, nk, sc, jn, alpha, cfl);
-}
-
-void launch_nk_commit(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk) {
-    hipLaunchKernelGGL(DIG_NV(g, k_nk_commit), cells_grid(g.nt), dim3(kDigThreads), 0, s, g, w, nk);
+    const dim3 gr = cells_grid(g.nt), bl(kDigThreads);
+    hipLaunchKernelGGL(DIG_NV(g, k_nk_try), gr, bl, 0, s, g, w, nk, sc, jn, alpha, cfl);
+    hipLaunchKernelGGL(DIG_NV(g, k_nk_commit), gr, bl, 0, s, g, w, nk);
 }
 
 // Batch: one workgroup per case sums its FV mass over its internal cells in

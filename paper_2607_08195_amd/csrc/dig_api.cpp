@@ -26,8 +26,15 @@ struct DigState {
     bool closed = true;  // no inflow or outflow boundary: the solve's mass is rescaled to the particles'
 };
 
+static void nk_release(NkWork& k) {
+    if (k.host) (void)hipHostFree(k.host);
+    for (hipEvent_t e : k.ev)
+        if (e) (void)hipEventDestroy(e);
+}
+
 void dig_release(dsmc_ctx c) {
     // device arrays belong to the context's allocation list
+    if (c->dig) nk_release(c->dig->nk);
     delete c->dig;
     c->dig = nullptr;
 }
@@ -483,15 +490,19 @@ dsmc_status ensure_nk(dsmc_ctx c, int m) {
     DigState* d = c->dig;
     if (d->nk.m >= m) return DSMC_OK;
     NkWork& k = d->nk;
-    for (double* q : {k.V, k.w, k.U, k.Ut, k.R0, k.Rp, k.part, k.red, k.y}) dev_free(c, q);
+    for (double* q : {k.V, k.w, k.U, k.Ut, k.R0, k.Rp, k.part, k.red, k.y, k.gm}) dev_free(c, q);
     dev_free(c, k.flag);
+    nk_release(k);
     k = NkWork{};
     const size_t n = (size_t)dig_nv(c) * c->nt;
     const size_t nblk = ((size_t)c->nt + kDigThreads - 1) / kDigThreads;
     const bool ok = alloc_n(c, k.V, n * (m + 1)) && alloc_n(c, k.w, n) && alloc_n(c, k.U, n) && alloc_n(c, k.Ut, n) &&
-                    alloc_n(c, k.R0, n) && alloc_n(c, k.Rp, n) && alloc_n(c, k.part, nblk * (m + 1)) &&
-                    alloc_n(c, k.red, (size_t)kNkRedSize(m)) && alloc_n(c, k.y, (size_t)m) && alloc_n(c, k.flag, 1);
+                    alloc_n(c, k.R0, n) && alloc_n(c, k.Rp, n) && alloc_n(c, k.part, nblk * (m + 2)) &&
+                    alloc_n(c, k.red, (size_t)kNkRedSize(m)) && alloc_n(c, k.y, (size_t)m) &&
+                    alloc_n(c, k.gm, (size_t)kNkGmSize(m)) && alloc_n(c, k.flag, 1);
     if (!ok) return fail(c, DSMC_E_OOM, "device allocation of the Krylov basis failed");
+    HIP_TRY(c, hipHostMalloc((void**)&k.host, sizeof(double) * kNkHostSlot * (1 + kNkAhead), 0));
+    for (hipEvent_t& e : k.ev) HIP_TRY(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
     k.m = m;
     return DSMC_OK;
 }
@@ -507,8 +518,9 @@ dsmc_status ensure_nk(dsmc_ctx c, int m) {
 // times, then the solve fails.  The stopping test is the marching's (the
 // density residual norm, with rotation the rotational-energy residual too,
 // against eps_m times its first value), taken at the start of each Newton
-// step; iters counts the updates.  Host round trips: one per Newton step,
-// one per GMRES step and one per trial update.
+// step; iters counts the updates.  The device ends a GMRES cycle by itself; the
+// host keeps kNkAhead steps in the stream and waits once per Newton step
+// (once more for each shortened update).
 dsmc_status run_solve_nk(dsmc_ctx c, const dig_params* p, dig_report* r) {
     DigState* d = c->dig;
     hipStream_t s = c->stream;
@@ -516,15 +528,12 @@ dsmc_status run_solve_nk(dsmc_ctx c, const dig_params* p, dig_report* r) {
     dsmc_status st = ensure_nk(c, m);
     if (st != DSMC_OK) return st;
     NkWork& nk = d->nk;
-    const int nv = dig_nv(c);
-    const double n = (double)nv * c->nt;
     const double R = kBoltzmann / c->mass;
     const double rho0 = c->mass * c->n0, a2 = R * c->T0, a0 = std::sqrt(a2);
     NkScale sc{};
     sc.s[0] = rho0;
     sc.s[1] = sc.s[2] = sc.s[3] = rho0 * a0;
     sc.s[4] = sc.s[5] = rho0 * a2;
-    std::vector<double> red((size_t)kNkRedSize(m)), H((size_t)(m + 1) * m), cs(m), sn(m), gv(m + 1), y(m);
     launch_dig_ctl_reset(s, d->w.ctl);
     double cfl = p->cfl, bprev = 0.0, lin = 0.0;
     bool failed = false;
@@ -533,88 +542,64 @@ dsmc_status run_solve_nk(dsmc_ctx c, const dig_params* p, dig_report* r) {
     // DSMC_NK_TRACE=1: one line per Newton step on stderr
     const char* tr = std::getenv("DSMC_NK_TRACE");
     const bool trace = tr && tr[0] == '1';
-    auto fetch = [&](int32_t* flag) -> dsmc_status {
-        HIP_TRY(c, hipMemcpyAsync(red.data(), nk.red, sizeof(double) * red.size(), hipMemcpyDeviceToHost, s));
-        if (flag) HIP_TRY(c, hipMemcpyAsync(flag, nk.flag, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(c, hipStreamSynchronize(s));
-        HIP_TRY(c, hipGetLastError());
+    const volatile double* start = nk.host;
+    auto step_done = [&](int j, int* stop) -> dsmc_status {
+        HIP_TRY(c, hipEventSynchronize(nk.ev[j % kNkAhead]));
+        const volatile double* q = nk.host + kNkHostSlot * (1 + j % kNkAhead);
+        *stop = (int)q[0];
+        lin = q[1];
         return DSMC_OK;
     };
+    if (p->n_m > 0) launch_nk_begin(s, d->g, d->w, nk, sc, 0, p->eps_m);
+    HIP_TRY(c, hipStreamSynchronize(s));
     for (k = 0; k < p->n_m; ++k) {
-        launch_nk_begin(s, d->g, d->w, nk, sc, k, p->eps_m);
-        HIP_TRY(c, hipMemcpyAsync(&h, d->w.ctl, sizeof h, hipMemcpyDeviceToHost, s));
-        if ((st = fetch(nullptr)) != DSMC_OK) return st;
-        if (h.conv) break;
-        const double beta = std::sqrt(red[kNkBeta2(m)]);
+        if (start[0] == 1.0) break;
+        const double beta = std::sqrt(start[1]), res = start[2], res0 = start[3];
         if (k > 0) {
             double f = bprev / beta;
             if (lin > kNkLinPoor && f > 0.5) f = 0.5;
             cfl = std::min(kNkCflMax, std::max(p->cfl, cfl * f));
         }
         bprev = beta;
-        HIP_TRY(c, hipMemsetAsync(nk.flag, 0, sizeof(int32_t), s));
         launch_nk_scale(s, d->g, d->w, nk, cfl, kNkFd);
-        std::fill(H.begin(), H.end(), 0.0);
-        gv[0] = beta;
-        int jn = 0;
-        for (int j = 0; j < m; ++j) {
-            launch_nk_arnoldi(s, d->g, d->w, nk, sc, j, cfl, kNkFd);
-            int32_t flag = 0;
-            if ((st = fetch(&flag)) != DSMC_OK) return st;
-            if (flag) {
-                failed = true;
-                break;
-            }
-            for (int i = 0; i <= j; ++i) H[(size_t)i * m + j] = (0.0 + red[kNkH1(m) + i]) + red[kNkH2(m) + i];
-            const double hn = std::sqrt(red[kNkHn2(m)]);
-            H[(size_t)(j + 1) * m + j] = hn;
-            for (int i = 0; i < j; ++i) {
-                const double a = H[(size_t)i * m + j], b = H[(size_t)(i + 1) * m + j];
-                H[(size_t)i * m + j] = cs[i] * a + sn[i] * b;
-                H[(size_t)(i + 1) * m + j] = -sn[i] * a + cs[i] * b;
-            }
-            const double a = H[(size_t)j * m + j], b = H[(size_t)(j + 1) * m + j];
-            const double rr = std::sqrt(a * a + b * b);
-            cs[j] = rr > 0 ? a / rr : 1.0;
-            sn[j] = rr > 0 ? b / rr : 0.0;
-            H[(size_t)j * m + j] = rr;
-            H[(size_t)(j + 1) * m + j] = 0.0;
-            gv[j + 1] = -sn[j] * gv[j];
-            gv[j] = cs[j] * gv[j];
-            jn = j + 1;
-            ++nkry;
-            if (std::fabs(gv[j + 1]) <= kNkEta * beta || !(hn > 0)) break;
+        int jn = 0, stop = 0;
+        for (int j = 0; j < m && !stop; ++j) {
+            launch_nk_arnoldi(s, d->g, d->w, nk, sc, j, cfl, kNkFd, kNkEta);
+            HIP_TRY(c, hipEventRecord(nk.ev[j % kNkAhead], s));
+            if (j + 1 < kNkAhead) continue;
+            jn = j + 2 - kNkAhead;
+            if ((st = step_done(jn - 1, &stop)) != DSMC_OK) return st;
         }
+        while (!stop && jn < m) {
+            ++jn;
+            if ((st = step_done(jn - 1, &stop)) != DSMC_OK) return st;
+        }
+        HIP_TRY(c, hipGetLastError());
+        nkry += stop == 2 ? jn - 1 : jn;
         if (trace)
             std::fprintf(stderr, "nk step %d: density residual %.3e of the first, |b| %.4e, cfl %.3e, gmres %d, "
-                         "linear residual %.3e\n", k, h.res0 > 0 ? h.res / h.res0 : 0.0, beta, cfl, jn,
-                         std::fabs(gv[jn]) / beta);
-        if (failed) break;
-        lin = std::fabs(gv[jn]) / beta;
-        for (int i = jn - 1; i >= 0; --i) {
-            double t = gv[i];
-            for (int l = i + 1; l < jn; ++l) t -= H[(size_t)i * m + l] * y[l];
-            y[i] = t / H[(size_t)i * m + i];
+                         "linear residual %.3e\n", k, res0 > 0 ? res / res0 : 0.0, beta, cfl, jn, lin);
+        if (stop == 2) {
+            failed = true;
+            break;
         }
-        HIP_TRY(c, hipMemcpyAsync(nk.y, y.data(), sizeof(double) * jn, hipMemcpyHostToDevice, s));
         double alpha = 1.0;
         bool accepted = false;
         for (int tries = 0; tries <= kNkHalvings && !accepted; ++tries) {
-            HIP_TRY(c, hipMemsetAsync(nk.flag, 0, sizeof(int32_t), s));
+            launch_nk_solve(s, d->w, nk, jn);
             launch_nk_try(s, d->g, d->w, nk, sc, jn, alpha, cfl);
-            int32_t flag = 0;
-            HIP_TRY(c, hipMemcpyAsync(&flag, nk.flag, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-            HIP_TRY(c, hipStreamSynchronize(s));
-            if (!flag)
-                accepted = true;
+            if (k + 1 < p->n_m)
+                launch_nk_begin(s, d->g, d->w, nk, sc, k + 1, p->eps_m);
             else
-                alpha = 0.5 * alpha;
+                launch_nk_report(s, d->g, d->w, nk);
+            HIP_TRY(c, hipStreamSynchronize(s));
+            accepted = start[0] != 2.0;
+            if (!accepted) alpha = 0.5 * alpha;
         }
         if (!accepted) {
             failed = true;
             break;
         }
-        launch_nk_commit(s, d->g, d->w, nk);
     }
     HIP_TRY(c, hipGetLastError());
     h = read_ctl(c, &st);

@@ -136,3 +136,56 @@ def test_newton_krylov_parameters_checked(D):
     out, rep = g.dig_solve(prim, hot, n_m=3, cfl=10.0, solver=1, krylov=10, eps_m=0.0)
     assert rep["iters"] == 3 and not rep["failed"]
     g.close()
+
+
+@pytest.mark.parametrize("n_hex", [3, 22, 23])  # 1, 250 and 286 blocks of partial sums, 256 a round of the sum
+def test_partial_sums_match_oracle(D, n_hex):
+    wl = W.cavity(n_hex=n_hex, Kn=0.01, ppc=1, lid_speed=50.0, jitter=0.1, mesh_seed=1)
+    o = Oracle(wl, fill=False)
+    o.set_reference(wl.run.n0, wl.run.T0)
+    g = D.Simulation(wl)
+    prim, hot = _noisy(o, wl, 5)
+    kw = dict(n_m=2, eps_m=0.0, cfl=10.0, solver=1, krylov=6)
+    pg, rg = g.dig_solve(prim, hot, **kw)
+    po, ro = o.dig_solve(prim, hot, **kw)
+    assert [rg[k] for k in ("iters", "krylov_steps", "failed")] == [ro[k] for k in ("iters", "krylov_steps", "failed")]
+    _col_close(pg, po, 1e-6, f"n_hex={n_hex}")
+    g.close()
+
+
+def test_smaller_basis_after_a_larger_one(D):
+    """The basis is kept at its largest size; a later solve with fewer GMRES
+    steps gives what a fresh context gives, bit for bit."""
+    wl, nv = _cases()["argon"]
+    o = Oracle(wl, fill=False)
+    o.set_reference(wl.run.n0, wl.run.T0)
+    prim, hot = _noisy(o, wl, nv)
+    small = dict(n_m=3, eps_m=0.0, cfl=10.0, solver=1, krylov=7)
+    a, b = D.Simulation(wl), D.Simulation(wl)
+    a.dig_solve(prim, hot, **dict(small, krylov=40))
+    (pa, ra), (pb, rb) = a.dig_solve(prim, hot, **small), b.dig_solve(prim, hot, **small)
+    assert np.array_equal(pa, pb) and ra == rb
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("n_m,cfl", [(1, 1e3), (6, 10.0)])
+def test_shortened_updates_match_oracle(D, n_m, cfl):
+    """A state far from any solution: updates that leave a cell non-physical
+    are halved (in the first step of the one case, in several of the other)."""
+    wl, nv = _cases()["argon"]
+    o = Oracle(wl, fill=False)
+    o.set_reference(wl.run.n0, wl.run.T0)
+    g = D.Simulation(wl)
+    prim, hot = _noisy(o, wl, nv)
+    rng = np.random.default_rng(3)
+    prim[:, 0] *= 1 + 0.9 * (rng.random(o.nt) - 0.5) * 2
+    prim[:, 4:] *= 1 + 0.9 * (rng.random((o.nt, nv - 4)) - 0.5) * 2
+    kw = dict(n_m=n_m, eps_m=0.0, cfl=cfl, solver=1, krylov=20)
+    pg, rg = g.dig_solve(prim, hot, **kw)
+    po, ro = o.dig_solve(prim, hot, **kw)
+    assert [rg[k] for k in ("iters", "failed")] == [ro[k] for k in ("iters", "failed")]
+    assert np.isfinite(pg).all() and (pg[:, 0] > 0).all() and (pg[:, 4] > 0).all()
+    if n_m == 1:
+        _col_close(pg, po, 1e-6, "one shortened update")
+    g.close()

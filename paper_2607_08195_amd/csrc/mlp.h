@@ -20,7 +20,8 @@ constexpr int kMlpB3 = kMlpW3 + kMlpHid * kMlpHid;
 constexpr int kMlpW4 = kMlpB3 + kMlpHid;                // W4[128][9]
 constexpr int kMlpB4 = kMlpW4 + kMlpHid * kMlpOut;
 constexpr int kMlpParams = kMlpB4 + kMlpOut;            // 35977
-constexpr int kMlpTile = 32;                            // rows per workgroup (two waves of 16)
+constexpr int kMlpTile = 32;                            // rows per workgroup of the gradient
+constexpr int kMlpPartial = (kMlpParams + 3) / 4 * 4;   // a tile's share of the gradient (16-byte stores)
 
 // BF16 operand copies of the weights, padded for the 16x16x32 products:
 // "f" copies are output-major (forward products), "b" copies input-major
@@ -41,19 +42,32 @@ constexpr int kMlpPackTotal = 128 * 32 + 128 * 128 * 2 + 16 * 128 + 128 * 128 * 
 void launch_mlp_pack(hipStream_t s, const float* params, uint16_t* packed);
 MlpDev mlp_dev_view(const float* params, const uint16_t* packed);
 MlpDev mlp_handle_view(dsmc_mlp_s* net);
-// Forward on n rows of x[n][13] (FP32) -> y[n][9]; rows may be gathered by idx.
-void launch_mlp_forward(hipStream_t s, const MlpDev& m, const float* x, const int32_t* idx, int64_t n, float* y);
-// Forward + backward of the mean squared error over the n rows; per-block
-// gradient partials [blocks][kMlpParams] and loss partials [blocks].
+// A minibatch: rows drawn with replacement from [0, rows) (off: the rows given).
+struct MlpBatch {
+    RngKey key;
+    uint32_t step;
+    int64_t rows;
+    int on;
+};
+struct MlpAdam {
+    float lr, b1, b2, eps, c1, c2;  // c = 1 - b^step
+};
+MlpAdam mlp_adam(int step, float lr, float b1, float b2, float eps);
+// Forward on n rows of x[n][13] (FP32) -> y[n][9].
+void launch_mlp_forward(hipStream_t s, const MlpDev& m, const float* x, int64_t n, float* y);
+// Forward + backward of the mean squared error over the n rows; per-tile
+// gradient partials [tiles][kMlpPartial] and loss partials [tiles].
 int64_t mlp_blocks(int64_t n);
-void launch_mlp_grad(hipStream_t s, const MlpDev& m, const float* x, const float* t, const int32_t* idx, int64_t n,
+void launch_mlp_grad(hipStream_t s, const MlpDev& m, const float* x, const float* t, const MlpBatch& batch, int64_t n,
                      float* partial, float* loss_partial);
-// grad = sum of the block partials; *loss = (sum of the loss partials) / denom
+// grad = sum of the tiles' partials; *loss = (sum of the loss partials) / denom
 void launch_mlp_reduce(hipStream_t s, const float* partial, const float* loss_partial, int64_t nblk, float* grad,
                        double* loss, double denom = 1.0);
-void launch_mlp_adam(hipStream_t s, float* params, const float* grad, float* m, float* v, int step, float lr,
-                     float b1, float b2, float eps);
+// The optimiser's step and the operand copies, from a gradient or from the partials.
+void launch_mlp_adam(hipStream_t s, float* params, const float* grad, float* m, float* v, const MlpAdam& a,
+                     uint16_t* packed);
+void launch_mlp_step(hipStream_t s, const float* partial, const float* loss_partial, int64_t nblk, double* loss,
+                     float* params, float* m, float* v, const MlpAdam& a, uint16_t* packed);
 void launch_mlp_init(hipStream_t s, float* params, RngKey key);
-void launch_mlp_batch(hipStream_t s, RngKey key, uint32_t step, int64_t n, int64_t batch, int32_t* idx);
 
 }  // namespace dsmcx

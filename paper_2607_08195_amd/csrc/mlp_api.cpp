@@ -31,8 +31,6 @@ struct dsmc_mlp_s {
     float* loss_partial = nullptr;
     int64_t cap_blocks = 0;
     float* grad = nullptr;
-    int32_t* idx = nullptr;
-    int64_t cap_idx = 0;
     double* loss = nullptr;
     int64_t cap_loss = 0;
 };
@@ -106,7 +104,7 @@ dsmc_status ensure_blocks(dsmc_mlp n, int64_t blocks) {
         mlp_free(n, n->partial);
         mlp_free(n, n->loss_partial);
         const int64_t c = std::max<int64_t>(blocks, 2 * n->cap_blocks);
-        n->partial = (float*)mlp_alloc(n, sizeof(float) * kMlpParams * (size_t)c);
+        n->partial = (float*)mlp_alloc(n, sizeof(float) * kMlpPartial * (size_t)c);
         n->loss_partial = (float*)mlp_alloc(n, sizeof(float) * (size_t)c);
         if (!n->partial || !n->loss_partial) {
             n->cap_blocks = 0;
@@ -121,11 +119,11 @@ MlpDev view(dsmc_mlp n) { return mlp_dev_view(n->params, n->packed); }
 
 // Scratch of dsmc_mlp_backward_noalloc, one copy per device for the life of
 // the process: the per-block gradient partials of at most
-// DSMC_MLP_NOALLOC_MAX_ROWS rows ([blocks][kMlpParams] floats) followed by
+// DSMC_MLP_NOALLOC_MAX_ROWS rows ([blocks][kMlpPartial] floats) followed by
 // the per-block loss partials.  Every block writes its whole partial, so
 // nothing has to start at zero.
 constexpr int64_t kNoAllocBlocks = DSMC_MLP_NOALLOC_MAX_ROWS / kMlpTile;
-constexpr size_t kNoAllocLossOffset = ((sizeof(float) * kMlpParams * kNoAllocBlocks + 255) / 256) * 256;
+constexpr size_t kNoAllocLossOffset = ((sizeof(float) * kMlpPartial * kNoAllocBlocks + 255) / 256) * 256;
 constexpr size_t kNoAllocBytes = kNoAllocLossOffset + sizeof(float) * kNoAllocBlocks;
 static_assert(DSMC_MLP_NOALLOC_MAX_ROWS % kMlpTile == 0, "whole tiles");
 
@@ -251,7 +249,7 @@ dsmc_status dsmc_mlp_forward(dsmc_mlp n, const float* x, int64_t rows, float* y,
         dx = n->x;
         dy = n->y;
     }
-    launch_mlp_forward(n->stream, view(n), dx, nullptr, rows, dy);
+    launch_mlp_forward(n->stream, view(n), dx, rows, dy);
     MLP_TRY(n, hipGetLastError());
     if (!on_device)
         MLP_TRY(n, hipMemcpyAsync(y, dy, sizeof(float) * kMlpOut * rows, hipMemcpyDeviceToHost, n->stream));
@@ -268,7 +266,7 @@ dsmc_status dsmc_mlp_backward(dsmc_mlp n, const float* x, const float* t, int64_
     if (!grow(n, n->loss, n->cap_loss, 1)) return mfail(n, DSMC_E_OOM, "device allocation failed");
     MLP_TRY(n, hipMemcpyAsync(n->x, x, sizeof(float) * kMlpIn * rows, hipMemcpyHostToDevice, n->stream));
     MLP_TRY(n, hipMemcpyAsync(n->t, t, sizeof(float) * kMlpOut * rows, hipMemcpyHostToDevice, n->stream));
-    launch_mlp_grad(n->stream, view(n), n->x, n->t, nullptr, rows, n->partial, n->loss_partial);
+    launch_mlp_grad(n->stream, view(n), n->x, n->t, MlpBatch{}, rows, n->partial, n->loss_partial);
     launch_mlp_reduce(n->stream, n->partial, n->loss_partial, mlp_blocks(rows), n->grad, n->loss);
     MLP_TRY(n, hipGetLastError());
     MLP_TRY(n, hipMemcpyAsync(grad, n->grad, sizeof(float) * kMlpParams, hipMemcpyDeviceToHost, n->stream));
@@ -293,7 +291,7 @@ dsmc_status dsmc_mlp_backward_noalloc(dsmc_mlp n, const float* x, const float* t
     if (!base) return mfail(n, DSMC_E_DEVICE, "the scratch of this device has no address");
     float* partial = (float*)base;
     float* loss_partial = (float*)((unsigned char*)base + kNoAllocLossOffset);
-    launch_mlp_grad(n->stream, view(n), x, t, nullptr, rows, partial, loss_partial);
+    launch_mlp_grad(n->stream, view(n), x, t, MlpBatch{}, rows, partial, loss_partial);
     launch_mlp_reduce(n->stream, partial, loss_partial, mlp_blocks(rows), grad, loss, (double)rows * kMlpOut);
     MLP_TRY(n, hipGetLastError());
     return DSMC_OK;
@@ -303,8 +301,7 @@ dsmc_status dsmc_mlp_adam_step(dsmc_mlp n, const float* grad, float lr, float b1
     if (!n || !grad) return mfail(n, DSMC_E_INVALID, "bad arguments");
     MLP_TRY(n, hipMemcpyAsync(n->grad, grad, sizeof(float) * kMlpParams, hipMemcpyHostToDevice, n->stream));
     n->step += 1;
-    launch_mlp_adam(n->stream, n->params, n->grad, n->m, n->v, n->step, lr, b1, b2, eps);
-    launch_mlp_pack(n->stream, n->params, n->packed);
+    launch_mlp_adam(n->stream, n->params, n->grad, n->m, n->v, mlp_adam(n->step, lr, b1, b2, eps), n->packed);
     MLP_TRY(n, hipGetLastError());
     MLP_TRY(n, hipStreamSynchronize(n->stream));
     return DSMC_OK;
@@ -321,17 +318,15 @@ dsmc_status dsmc_mlp_train(dsmc_mlp n, const float* x, const float* t, int64_t r
     if (st == DSMC_OK) st = ensure_blocks(n, mlp_blocks(b));
     if (st != DSMC_OK) return st;
     if (!grow(n, n->loss, n->cap_loss, std::max(1, p->steps))) return mfail(n, DSMC_E_OOM, "device allocation failed");
-    if (!full && !grow(n, n->idx, n->cap_idx, b)) return mfail(n, DSMC_E_OOM, "device allocation failed");
     MLP_TRY(n, hipMemcpyAsync(n->x, x, sizeof(float) * kMlpIn * rows, hipMemcpyHostToDevice, n->stream));
     MLP_TRY(n, hipMemcpyAsync(n->t, t, sizeof(float) * kMlpOut * rows, hipMemcpyHostToDevice, n->stream));
     const RngKey key{(uint32_t)(p->seed & 0xFFFFFFFFu), 0u};
     for (int s = 0; s < p->steps; ++s) {
-        if (!full) launch_mlp_batch(n->stream, key, (uint32_t)s, rows, b, n->idx);
-        launch_mlp_grad(n->stream, view(n), n->x, n->t, full ? nullptr : n->idx, b, n->partial, n->loss_partial);
-        launch_mlp_reduce(n->stream, n->partial, n->loss_partial, mlp_blocks(b), n->grad, n->loss + s);
+        launch_mlp_grad(n->stream, view(n), n->x, n->t, MlpBatch{key, (uint32_t)s, rows, full ? 0 : 1}, b, n->partial,
+                        n->loss_partial);
         n->step += 1;
-        launch_mlp_adam(n->stream, n->params, n->grad, n->m, n->v, n->step, p->lr, p->beta1, p->beta2, p->eps);
-        launch_mlp_pack(n->stream, n->params, n->packed);
+        launch_mlp_step(n->stream, n->partial, n->loss_partial, mlp_blocks(b), n->loss + s, n->params, n->m, n->v,
+                        mlp_adam(n->step, p->lr, p->beta1, p->beta2, p->eps), n->packed);
     }
     MLP_TRY(n, hipGetLastError());
     MLP_TRY(n, hipStreamSynchronize(n->stream));

@@ -207,3 +207,45 @@ def test_closure_in_couple_matches_oracle(D):
     assert np.allclose(g.dig_get("hot"), hot, rtol=1e-9, atol=1e-9 * np.abs(hot).max())
     net.close()
     g.close()
+
+
+@pytest.mark.parametrize("n", [33, 32768, 32769, 70001])
+def test_forward_tiles_agree(D, n):
+    """32-row tiles up to 32,768 rows, 64-row ones that the workgroups stride
+    over beyond: a row's result does not depend on the tile it falls in, bit
+    for bit, with inputs far into the SiLU's tails, infinities and NaN among
+    them."""
+    x = np.random.default_rng(12).standard_normal((n, 13)).astype(np.float32)
+    x[::7] *= 1e3
+    x[5] = np.inf
+    x[n - 1, 3] = np.nan
+    net = D.Mlp()
+    net.set_weights(_params(1, 3.0))
+    y = net.forward(x)
+    for a in sorted({0, 16, 32752, max(0, n - 40)}):
+        if a < n:
+            part = net.forward(x[a:a + 40])
+            assert np.array_equal(y[a:a + 40], part, equal_nan=True), a
+    assert np.isnan(y[n - 1]).all() and np.isfinite(y[6:n - 1]).all()
+    yo, _ = M.forward(_params(1, 3.0), x[6:32].astype(np.float64), bf16=True)
+    assert np.linalg.norm(y[6:32] - yo) <= 2e-3 * np.linalg.norm(yo)
+    net.close()
+
+
+@pytest.mark.parametrize("n", [1, 33, 513, 4097])
+def test_training_step_is_backward_then_adam(D, n):
+    """A training step (reduction, optimiser and operand copies in one kernel)
+    gives the weights, the loss and the next outputs of its parts, bit for bit."""
+    rng = np.random.default_rng(13)
+    x = rng.standard_normal((n, 13)).astype(np.float32)
+    t = rng.standard_normal((n, 9)).astype(np.float32)
+    a, b = D.Mlp(), D.Mlp()
+    a.set_weights(_params(14))
+    b.set_weights(_params(14))
+    rep = a.train(x, t, steps=1, batch=0, lr=1e-2)
+    loss, g = b.backward(x, t)
+    b.adam_step(g, lr=1e-2)
+    assert np.array_equal(a.get_weights(), b.get_weights()) and rep["loss_first"] == loss
+    assert np.array_equal(a.forward(x), b.forward(x))
+    a.close()
+    b.close()

@@ -272,11 +272,12 @@ dsmc_status run_step(dsmc_ctx c, int mask) {
             Timed t(c, kSlotScan);
             launch_scan(s, c->d_counts, c->nt, c->d_offsets, c->d_blocksums, c->d_sc, kScanCells);
         }
+        fuse = c->sort_variant != kSortScatter && (col || smp) && collide_fuses_gather(c->collide_variant);
         {
             Timed t(c, kSlotScatter);
-            launch_scatter<VT>(s, a, b, c->d_sc, c->d_offsets, c->d_rank, need, c->cap, c->d_sortperm, c->sort_variant);
+            launch_scatter<VT>(s, a, b, c->d_sc, c->d_offsets, c->d_rank, need, c->cap, c->d_sortperm,
+                               c->sort_variant == kSortScatter ? kSortScatter : fuse ? kSortFused : kSortGather);
         }
-        fuse = c->sort_variant == kSortFused && (col || smp) && collide_fuses_gather(c->collide_variant);
         if (c->sort_variant != kSortScatter && !fuse) {
             Timed t(c, kSlotGather);
             launch_gather<VT>(s, a, b, c->d_sc, c->d_sortperm, need);

@@ -549,9 +549,12 @@ constexpr int stage_cap(int wg) {
 // coalesced loads, and four lanes a cell rank its ids; then the candidate
 // pairs, the collisions and the sums (collide_cells).  A single cell beyond
 // the stage works on the particle store through a global order table.
-// With FUSED, the cells' slots of the sorted buffer p are first filled from
-// the unsorted buffer src through the gather permutation (slot -> source
-// index): the sort's gather done by the workgroup that then collides them.
+// With FUSED, the cells' slots of the sorted buffer p are filled from the
+// unsorted buffer src through the gather permutation (slot -> source index):
+// velocities and ids go through the stage, the rest passes through once the
+// window has been worked on, while other workgroups compute.  On the 40^3
+// cavity 486 us, against 367 for a gather of its own and 280 for this kernel
+// without (and 35 less in the permutation, which need not write the cells).
 // With IND (deferred sort) nothing is moved: slot d of the sorted order is
 // particle sortperm[d] of p.
 // Bound: VALU issue (16,700 wave instructions per 64 cells at 30 particles a
@@ -601,51 +604,6 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
         if (do_sample) load_sums<ROT>(sums, c, wave, cp, (int64_t)step > (int64_t)cp.n_ss);
     }
     __syncthreads();
-    if (FUSED) {
-        const int n = soff[CC];
-        // kFuseBatch particles per lane in flight: all loads of a batch are
-        // issued before its stores (the compiler cannot move a load of src
-        // above a store to p, which might alias it)
-        constexpr int kFuseBatch = 8;
-        for (int i0 = tid; i0 < n; i0 += kFuseBatch * kCollideLanes) {
-            int64_t j[kFuseBatch];
-            double x[kFuseBatch][3];
-            VT v[kFuseBatch][3];
-            uint32_t id[kFuseBatch];
-#pragma unroll
-            for (int b = 0; b < kFuseBatch; ++b) {
-                const int i = i0 + b * kCollideLanes;
-                j[b] = i < n ? sortperm[a + i] : 0;
-            }
-#pragma unroll
-            for (int b = 0; b < kFuseBatch; ++b) {
-                if (i0 + b * kCollideLanes < n) {
-                    x[b][0] = src.pos[3 * j[b]];
-                    x[b][1] = src.pos[3 * j[b] + 1];
-                    x[b][2] = src.pos[3 * j[b] + 2];
-                    v[b][0] = src.vel[3 * j[b]];
-                    v[b][1] = src.vel[3 * j[b] + 1];
-                    v[b][2] = src.vel[3 * j[b] + 2];
-                    id[b] = src.pid[j[b]];
-                }
-            }
-#pragma unroll
-            for (int b = 0; b < kFuseBatch; ++b) {
-                const int i = i0 + b * kCollideLanes;
-                if (i < n) {
-                    const int64_t d = a + i;
-                    p.pos[3 * d] = x[b][0];
-                    p.pos[3 * d + 1] = x[b][1];
-                    p.pos[3 * d + 2] = x[b][2];
-                    p.vel[3 * d] = v[b][0];
-                    p.vel[3 * d + 1] = v[b][1];
-                    p.vel[3 * d + 2] = v[b][2];
-                    p.pid[d] = id[b];
-                }
-            }
-        }
-        __syncthreads();
-    }
 #pragma unroll 1
     for (int k0 = 0; k0 < CC;) {
         // the cells from k0 on that fit the stage together (lane l looks at
@@ -656,6 +614,19 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
         if (k1 == k0) {
             // one cell beyond the stage: its order by comparison of all ids
             const int N = soff[k0 + 1] - w0;
+            if (FUSED) {
+                for (int k = tid; k < N; k += kCollideLanes) {
+                    const int64_t d = base + k, j = sortperm[d];
+                    for (int q = 0; q < 3; ++q) {
+                        p.pos[3 * d + q] = src.pos[3 * j + q];
+                        p.vel[3 * d + q] = src.vel[3 * j + q];
+                    }
+                    p.pid[d] = src.pid[j];
+                    p.cell[d] = c0 + k0;
+                    if (ROT) p.ir[d] = src.ir[j];
+                }
+                __syncthreads();
+            }
             for (int k = tid; k < N; k += kCollideLanes) {
                 const int32_t l = IND ? sortperm[base + k] : (int32_t)(base + k);
                 const uint32_t pk = p.pid[l];
@@ -682,15 +653,16 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
             for (int b = 0; b < kStageBatch; ++b) {
                 // past the window: its last particle again (no branch around a load)
                 x[b] = base + min(i0 + b * kCollideLanes, wn - 1);
-                if (IND) x[b] = sortperm[x[b]];
+                if (IND || FUSED) x[b] = sortperm[x[b]];
             }
+            const PartDev<VT>& from = FUSED ? src : p;
 #pragma unroll
             for (int b = 0; b < kStageBatch; ++b) {
-                id[b] = p.pid[x[b]];
-                v[b][0] = p.vel[3 * x[b]];
-                v[b][1] = p.vel[3 * x[b] + 1];
-                v[b][2] = p.vel[3 * x[b] + 2];
-                if (ROT) I[b] = p.ir[x[b]];
+                id[b] = from.pid[x[b]];
+                v[b][0] = from.vel[3 * x[b]];
+                v[b][1] = from.vel[3 * x[b] + 1];
+                v[b][2] = from.vel[3 * x[b] + 2];
+                if (ROT) I[b] = from.ir[x[b]];
             }
 #pragma unroll
             for (int b = 0; b < kStageBatch; ++b) {
@@ -702,6 +674,7 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
                     lv[3 * i + 2] = v[b][2];
                     if (ROT) li[i] = I[b];
                     if (IND) idx[i] = (uint32_t)x[b];
+                    if (FUSED) p.pid[base + i] = id[b];
                 }
             }
         }
@@ -732,7 +705,10 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
 #pragma unroll
                 for (int t = 0; t < kBatch; ++t) {
                     const int x = b0 + kLanes * t;
-                    if (x < N) ord[r[t]] = (uint16_t)(3 * (s0 + x));
+                    if (x < N) {
+                        ord[r[t]] = (uint16_t)(3 * (s0 + x));
+                        if (FUSED) p.cell[base + s0 + x] = c0 + lc;
+                    }
                 }
             }
         }
@@ -742,12 +718,35 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
         const int N = live ? soff[lane + 1] - soff[lane] : 0;
         const Staged<VT, IND> cv{lv, li, ord, idx, p.vel, p.ir};
         collide_cells<VSS, ROT>(cv, live, s0, N, c, wave, u.ps, tab, cp, step, do_collide, do_sample, f, sums);
-        if (!IND && do_collide) {
+        if (FUSED || (!IND && do_collide)) {
             // whole lines: written where they changed, 12 bytes here and
             // there, the same velocities took the memory several times as long
             for (int i = tid; i < 3 * wn; i += kCollideLanes) p.vel[3 * base + i] = lv[i];
             if (ROT)
                 for (int i = tid; i < wn; i += kCollideLanes) p.ir[base + i] = li[i];
+        }
+        if (FUSED) {
+            // positions only pass through (next read by the following step's move)
+            for (int i0 = tid; i0 < wn; i0 += kStageBatch * kCollideLanes) {
+                double x[kStageBatch][3];
+#pragma unroll
+                for (int b = 0; b < kStageBatch; ++b) {
+                    const int64_t j = sortperm[base + min(i0 + b * kCollideLanes, wn - 1)];
+                    x[b][0] = src.pos[3 * j];
+                    x[b][1] = src.pos[3 * j + 1];
+                    x[b][2] = src.pos[3 * j + 2];
+                }
+#pragma unroll
+                for (int b = 0; b < kStageBatch; ++b) {
+                    const int i = i0 + b * kCollideLanes;
+                    if (i < wn) {
+                        double* d = p.pos + 3 * (base + i);
+                        __builtin_nontemporal_store(x[b][0], d);
+                        __builtin_nontemporal_store(x[b][1], d + 1);
+                        __builtin_nontemporal_store(x[b][2], d + 2);
+                    }
+                }
+            }
         }
         k0 = k1;
         __syncthreads();  // the stage is filled again
@@ -773,13 +772,10 @@ static void launch_collide_g(hipStream_t s, PartDev<VT> p, const int32_t* offset
                            sc, perm, do_collide, do_sample, src, sortperm);
         return;
     }
-    if constexpr (!ROT) {
-        // a rotating gas never takes the fused gather (the host refuses that schedule)
-        if (gmode == kGatherFused) {
-            hipLaunchKernelGGL((k_collide_sample<VT, CC, WG, kGatherFused, VSS, ROT>), gr, bl, 0, s, p, offsets, cp,
-                               sc, perm, do_collide, do_sample, src, sortperm);
-            return;
-        }
+    if (gmode == kGatherFused) {
+        hipLaunchKernelGGL((k_collide_sample<VT, CC, WG, kGatherFused, VSS, ROT>), gr, bl, 0, s, p, offsets, cp, sc,
+                           perm, do_collide, do_sample, src, sortperm);
+        return;
     }
     hipLaunchKernelGGL((k_collide_sample<VT, CC, WG, kGatherNone, VSS, ROT>), gr, bl, 0, s, p, offsets, cp, sc, perm,
                        do_collide, do_sample, src, sortperm);

@@ -672,7 +672,8 @@ dsmc_status feedback_t(dsmc_ctx c) {
     launch_fill_i32(s, c->d_counts, 0, nt + 1);
     launch_dig_count_all(s, a.cell, c->d_sc, c->d_counts, c->d_rank, bound);
     launch_scan(s, c->d_counts, nt, c->d_offsets, c->d_blocksums, c->d_sc, kScanCells);
-    launch_scatter<VT>(s, a, b, c->d_sc, c->d_offsets, c->d_rank, bound, c->cap, c->d_sortperm, c->sort_variant);
+    launch_scatter<VT>(s, a, b, c->d_sc, c->d_offsets, c->d_rank, bound, c->cap, c->d_sortperm,
+                       c->sort_variant == kSortScatter ? kSortScatter : kSortGather);
     if (c->sort_variant != kSortScatter) launch_gather<VT>(s, a, b, c->d_sc, c->d_sortperm, bound);
     std::swap(c->A, c->B);
     c->np_bound = bound;

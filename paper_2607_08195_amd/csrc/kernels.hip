@@ -1036,7 +1036,7 @@ __global__ __launch_bounds__(256) void k_perm(const int32_t* cell, const Scalars
     if (c < 0) return;
     const int64_t d = (int64_t)offsets[c] + rank[i];
     perm[d] = (int32_t)i;
-    dst_cell[d] = c;  // the slot's cell, so that the gather need not load it
+    if (dst_cell) dst_cell[d] = c;  // the slot's cell, so that the gather need not load it
 }
 
 // The sorted order of a buffer that is already sorted: slot k holds
@@ -1378,7 +1378,7 @@ void launch_scatter(hipStream_t s, PartDev<VT> src, PartDev<VT> dst, const Scala
                     const uint32_t* rank, int64_t bound, int64_t cap, int32_t* perm, int variant) {
     if (variant != kSortScatter) {
         hipLaunchKernelGGL(k_perm, dim3(grid8(bound, 256)), dim3(256), 0, s, src.cell, sc, offsets, rank, perm,
-                           dst.cell, cap);
+                           variant == kSortFused ? (int32_t*)nullptr : dst.cell, cap);
     } else {
         hipLaunchKernelGGL(k_scatter<VT>, dim3(grid8(bound, 256)), dim3(256), 0, s, src, dst, sc, offsets, rank, cap);
     }

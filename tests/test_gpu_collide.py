@@ -82,3 +82,30 @@ def test_uneven_cells_match_oracle(D, n_hex, collide, sort, vel_fp32, gas):
         compare_sums(g.rot_sums(D.SAMPLE_STEADY)[0], o.rot_sums(0))
     compare_sums(g.sums(D.SAMPLE_STEADY)[0], o.sums(0))
     g.close()
+
+
+@pytest.mark.parametrize("vel_fp32,gas", [(1, "argon"), (0, "vss"), (1, "nitrogen"), (0, "nitrogen")])
+def test_gather_in_collide_matches_scatter(D, vel_fp32, gas):
+    """The whole particle (position, velocity, id, cell, rotational energy)
+    comes through the collide kernel's gather as it does through a scatter,
+    bit for bit, over cells of every size and a few steps of motion."""
+    sp = {"argon": W.Species(), "vss": W.Species(d_ref=4.11e-10, alpha=1.40),
+          "nitrogen": W.Species(mass=4.65e-26, omega=0.74, dof_rot=2, z_rot=2.59)}[gas]
+    wl = W.cavity(n_hex=5, Kn=0.1, ppc=20, vel_fp32=vel_fp32, n_ss=0, species=sp)
+    wl.run.dt *= 0.02  # the big cells' candidates grow with the square of their particles
+    x, v, cell, pid, ir = _state(wl, 5000)
+    smax = Oracle(wl).smax()
+    out = []
+    for sort in (0, 1):
+        g = D.Simulation(wl, fill=False, capacity=2 * len(cell))
+        g.set_tuning(15, 3, sort)
+        g.set_state(x, v, cell, pid, 0, len(cell), smax, ir=ir)
+        g.step_stages(STAGES)
+        first = g.state()
+        g.step(3)
+        out.append((first, g.state(), g.sums(D.SAMPLE_STEADY)[0]))
+        g.close()
+    for a, b in zip(out[0][:2], out[1][:2]):
+        for k in ("x", "v", "cell", "pid") + (("ir",) if sp.dof_rot else ()):
+            assert np.array_equal(a[k], b[k]), k
+    assert np.array_equal(out[0][2], out[1][2])

@@ -13,13 +13,15 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libdsmc.so")
 BUILD = os.path.join(HERE, "_build")
 
-SOURCES = ["kernels.hip", "collide.hip", "dig.hip", "mlp.hip", "api.cpp", "dig_api.cpp", "mlp_api.cpp", "mesh.cpp", "mixed.cpp"]
+SOURCES = ["kernels.hip", "collide.hip", "walls.hip", "dig.hip", "mlp.hip", "api.cpp", "dig_api.cpp", "mlp_api.cpp",
+           "mesh.cpp", "mixed.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-ffp-contract=off", "-fno-fast-math",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-result",
          "-I", INCLUDE, "-I", CSRC]
-# Loop-invariant constants hoisted out of the collide kernel's loops (the
-# coefficients of FP64 sine, cosine and power) would take all its registers
-EXTRA = {"collide.hip": ["-mllvm", "-disable-machine-licm"]}
+# Loop-invariant constants hoisted out of loops (the coefficients of FP64 sine,
+# cosine, logarithm and power) would take all registers of the collide kernel
+# and a wave per SIMD of the wall kernel
+EXTRA = {f: ["-mllvm", "-disable-machine-licm"] for f in ("collide.hip", "walls.hip")}
 
 
 def _compile(src, verbose):

@@ -330,7 +330,7 @@ __device__ __forceinline__ void exit_candidate(const double4& pl, int f, const W
 
 // Diffuse re-emission of a walker that has just reached boundary face bf
 // through local face fb (the wall becomes its entry face).
-template <class VT>
+template <class VT, bool SURF = true>
 __device__ __forceinline__ void diffuse_reemit(const MeshDev& m, Walker& w, int bf, int fb, uint32_t step,
                                                RngKey key) {
     const GroupDev& g = m.groups[m.bf_group[bf]];
@@ -349,7 +349,7 @@ __device__ __forceinline__ void diffuse_reemit(const MeshDev& m, Walker& w, int 
     w.v2 = round_store<VT>((vn * fr[2] + g.sw * (g1 * fr[5] + g2 * fr[8])) + g.u[2]);
     // the re-emitted molecule's rotation is in equilibrium at the wall
     const double Inew = m.rot ? -g.kT * log(u01(r1.w[2], r1.w[3])) : 0.0;
-    surface_hit(m, bf, step, a0, a1, a2, w.v0, w.v1, w.v2, m.rot ? w.ir - Inew : 0.0);
+    if (SURF) surface_hit(m, bf, step, a0, a1, a2, w.v0, w.v1, w.v2, m.rot ? w.ir - Inew : 0.0);
     if (m.rot) w.ir = Inew;
     ++w.hits;
     ++w.walls;
@@ -455,6 +455,33 @@ __device__ __forceinline__ int hop_once(const MeshDev& m, Walker& w, uint32_t st
         return 1;
     }
     return -1;
+}
+
+__device__ __forceinline__ int wave_sum(int v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// Sum four counters over the block and add them to global counters.
+__device__ __forceinline__ void block_counters(int a, int b, int c, int d, unsigned long long* ga,
+                                               unsigned long long* gb, unsigned long long* gc,
+                                               unsigned long long* gd) {
+    __shared__ int red[4][16];
+    a = wave_sum(a); b = wave_sum(b); c = wave_sum(c); d = wave_sum(d);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (lane == 0) { red[0][w] = a; red[1][w] = b; red[2][w] = c; red[3][w] = d; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int nw = (blockDim.x + 63) >> 6;
+        int s[4] = {0, 0, 0, 0};
+        for (int k = 0; k < nw; ++k)
+            for (int j = 0; j < 4; ++j) s[j] += red[j][k];
+        if (s[0]) atomicAdd(ga, (unsigned long long)s[0]);
+        if (s[1]) atomicAdd(gb, (unsigned long long)s[1]);
+        if (s[2]) atomicAdd(gc, (unsigned long long)s[2]);
+        if (s[3]) atomicAdd(gd, (unsigned long long)s[3]);
+    }
 }
 
 }  // namespace dsmcx

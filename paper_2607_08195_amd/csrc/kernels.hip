@@ -24,33 +24,6 @@ __device__ __forceinline__ int64_t xcd_block() {
     return (int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3);
 }
 
-__device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// Sum four counters over the block and add them to global counters.
-__device__ __forceinline__ void block_counters(int a, int b, int c, int d, unsigned long long* ga,
-                                               unsigned long long* gb, unsigned long long* gc,
-                                               unsigned long long* gd) {
-    __shared__ int red[4][16];
-    a = wave_sum(a); b = wave_sum(b); c = wave_sum(c); d = wave_sum(d);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) { red[0][w] = a; red[1][w] = b; red[2][w] = c; red[3][w] = d; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const int nw = (blockDim.x + 63) >> 6;
-        int s[4] = {0, 0, 0, 0};
-        for (int k = 0; k < nw; ++k)
-            for (int j = 0; j < 4; ++j) s[j] += red[j][k];
-        if (s[0]) atomicAdd(ga, (unsigned long long)s[0]);
-        if (s[1]) atomicAdd(gb, (unsigned long long)s[1]);
-        if (s[2]) atomicAdd(gc, (unsigned long long)s[2]);
-        if (s[3]) atomicAdd(gd, (unsigned long long)s[3]);
-    }
-}
-
 // Slot of a particle in its cell's histogram bin, aggregated over the
 // workgroup: the lanes' destination cells go into an LDS hash table
 // (open addressing, twice as many entries as lanes, so a probe always ends),
@@ -609,77 +582,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void
         }
         p.cell[i] = cc;
         if (!(f & 2) && cc >= 0) rank[i] = (uint32_t)atomicAdd(&counts[cc], 1);
-    }
-    block_counters(hops, walls, rem, lost, &ctr->hops, &ctr->walls, &ctr->removed, &ctr->lost);
-}
-
-// Takes queue entry e into the lane's walker: a particle parked at a diffuse
-// wall is re-emitted there, one parked in flight resumes with its velocity.
-template <class VT>
-__device__ __forceinline__ int64_t queue_take(const MeshDev& m, const PartDev<VT>& p, const WallQueue& q, int64_t e,
-                                              uint32_t step, RngKey key, Walker& w, RngKey& kp) {
-    const int64_t i = q.idx[e];
-    const int meta = q.meta[e];
-    const double tq = q.t[e];
-    w.x0 = p.pos[3 * i]; w.x1 = p.pos[3 * i + 1]; w.x2 = p.pos[3 * i + 2];
-    w.c = p.cell[i]; w.pid = p.pid[i]; w.t = tq < 0 ? -tq : tq;
-    w.entry = meta & 3; w.hits = (meta >> 2) & 1023; w.nhop = (meta >> 12) & 1023; w.walls = (meta >> 22) & 1023;
-    if (m.rot) w.ir = p.ir[i];
-    kp = key;
-    double dtp = 0.0;
-    case_params(m.cell_case, m.cases, w.c, kp, dtp);
-    // a walker parked in flight carries a negative time; one parked at a
-    // diffuse wall entered through a boundary face.  Both tests are made:
-    // a non-finite time (a particle whose position lies in no cell) has no
-    // usable sign, and only a boundary face may be re-emitted from.
-    const int code = m.nbr[4 * w.c + w.entry];
-    if (tq < 0 || code >= 0) {
-        w.v0 = (double)p.vel[3 * i]; w.v1 = (double)p.vel[3 * i + 1]; w.v2 = (double)p.vel[3 * i + 2];
-    } else {
-        // surface sampling needs the velocity the particle reached the wall with
-        if (m.surf) {
-            w.v0 = (double)p.vel[3 * i]; w.v1 = (double)p.vel[3 * i + 1]; w.v2 = (double)p.vel[3 * i + 2];
-        }
-        diffuse_reemit<VT>(m, w, -1 - code, w.entry, step, kp);
-    }
-    return i;
-}
-
-// Finishes the step of the parked particles, one queue entry per lane at a
-// time.  Workgroups take the queue parts round-robin (gridDim.x is a
-// multiple of kQueueParts) and stride through their part.  (Refilling lanes
-// from the queue as their particles finish was measured slower: the refill
-// brings the scattered loads and the wall re-emission into every pass of
-// the hop loop.)
-template <class VT>
-__global__ __launch_bounds__(256) void k_move_walls(MeshDev m, PartDev<VT> p, const Scalars* sc, int32_t* counts,
-                                                   uint32_t* rank, Counters* ctr, RngKey key, WallQueue q) {
-    const int part = (int)(blockIdx.x % kQueueParts);
-    const int64_t nq = (int64_t)q.n[(size_t)part * kQueueStride];
-    const int64_t stride = (int64_t)(gridDim.x / kQueueParts) * blockDim.x;
-    const uint32_t step = sc->step;
-    int hops = 0, walls = 0, rem = 0, lost = 0;
-    for (int64_t k = (int64_t)(blockIdx.x / kQueueParts) * blockDim.x + threadIdx.x; k < nq; k += stride) {
-        Walker w;
-        RngKey kp;
-        const int64_t i = queue_take<VT>(m, p, q, part * q.part + k, step, key, w, kp);
-        int st;
-        do {
-            st = hop_once<VT, false, true>(m, w, step, kp);  // parked walkers have an entry face
-        } while (st < 0);
-        hops += w.nhop;
-        walls += w.walls;
-        p.pos[3 * i] = w.x0; p.pos[3 * i + 1] = w.x1; p.pos[3 * i + 2] = w.x2;
-        p.vel[3 * i] = (VT)w.v0; p.vel[3 * i + 1] = (VT)w.v1; p.vel[3 * i + 2] = (VT)w.v2;
-        if (m.rot) p.ir[i] = w.ir;
-        if (st == 0) {
-            p.cell[i] = w.c;
-            rank[i] = (uint32_t)atomicAdd(&counts[w.c], 1);
-        } else {
-            p.cell[i] = -1;
-            rem += st == 1;
-            lost += st == 2;
-        }
     }
     block_counters(hops, walls, rem, lost, &ctr->hops, &ctr->walls, &ctr->removed, &ctr->lost);
 }
@@ -1333,12 +1235,6 @@ void launch_move(hipStream_t s, const MeshDev& m, PartDev<VT> p, const Scalars* 
     }
 }
 
-template <class VT>
-void launch_move_walls(hipStream_t s, const MeshDev& m, PartDev<VT> p, const Scalars* sc, int32_t* counts,
-                       uint32_t* rank, Counters* ctr, RngKey key, WallQueue wq) {
-    hipLaunchKernelGGL(k_move_walls<VT>, dim3(1024), dim3(256), 0, s, m, p, sc, counts, rank, ctr, key, wq);
-}
-
 bool move_parks_walls(int variant) {
     return variant == kMoveDefer4 || variant == kMoveDefer5 || variant == kMoveDefer6 || variant == kMoveDefer8 ||
            variant == kMoveCap4 || variant == kMoveCap5 || variant == kMoveCap6 || variant == kMoveFace3 || variant == kMoveFace3W8 ||
@@ -1440,8 +1336,6 @@ void launch_fill_f64(hipStream_t s, double* p, double v, int64_t n) {
                                          double, int64_t, int64_t);                                         \
     template void launch_scatter<VT>(hipStream_t, PartDev<VT>, PartDev<VT>, const Scalars*, const int32_t*, \
                                      const uint32_t*, int64_t, int64_t, int32_t*, int);                                           \
-    template void launch_move_walls<VT>(hipStream_t, const MeshDev&, PartDev<VT>, const Scalars*, int32_t*,  \
-                                        uint32_t*, Counters*, RngKey, WallQueue);                           \
     template void launch_gather<VT>(hipStream_t, PartDev<VT>, PartDev<VT>, const Scalars*, const int32_t*,  \
                                     int64_t);
 

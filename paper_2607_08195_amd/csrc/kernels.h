@@ -12,6 +12,7 @@ constexpr int kNMom = 13;               // S0, S1(3), S2(6), S3(3)
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanBlock = kScanThreads * kScanItems;
+constexpr int kScanTopBlocks = 128;    // more blocks: their sums are scanned by a kernel of its own
 constexpr int kMoveBatch = 512;        // particles per wave in the move kernel
 constexpr int kCollideLanes = 256;      // four waves
 constexpr int kPairSlots = kCollideLanes;  // candidate pairs drawn at once

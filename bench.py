@@ -35,18 +35,19 @@ sys.path.insert(0, ROOT)
 BYTES = {
     "move": lambda np_, nt, f: np_ * (72.0 + (12.0 + 8.0 * f["rot"]) * f["walls"]),
     "scan": lambda np_, nt, f: nt * 8.0,
-    "sort": lambda np_, nt, f: np_ * (88.0 + 16.0 * f["rot"]),
-    "collide_sample": lambda np_, nt, f: (np_ * (16.0 + 12.0 * f["touched"] + f["rot"] * (8.0 + 8.0 * f["touched"]))
-                                          + nt * (224.0 + 64.0 * f["rot"])),
+    # one stage: the default schedule's collide kernel does the sort's gather
+    "sort_collide_sample": lambda np_, nt, f: (np_ * (104.0 + 16.0 * f["rot"] + 12.0 * f["touched"]
+                                                      + f["rot"] * (8.0 + 8.0 * f["touched"]))
+                                               + nt * (224.0 + 64.0 * f["rot"])),
 }
-STAGES = {"move": ["move", "move_walls"], "scan": ["scan"], "sort": ["sort_perm", "sort_gather"],
-          "collide_sample": ["collide_sample"]}
+STAGES = {"move": ["move", "move_walls"], "scan": ["scan"],
+          "sort_collide_sample": ["sort_perm", "sort_gather", "collide_sample"]}
 
 # rocprofv3 --pmc measurements of the dominant stage's kernels (FETCH_SIZE +
 # WRITE_SIZE per step, summed over the stage's kernels and scaled by the
 # copy-kernel calibration) and the source digest they were taken on; the
 # traffic figure is reported only while the digest matches.
-TRAFFIC = {"stage": "move", "digest": "f678485dc442d1cf", "bytes_per_launch": 1255226834,
+TRAFFIC = {"stage": "move", "digest": "337bfdfe9033f966", "bytes_per_launch": 1253847040,
            "workload": "cavity_40^3x6_Kn0.1", "source": "profiles/step_kernels_cavity40.md"}
 
 
@@ -55,7 +56,7 @@ TRAFFIC = {"stage": "move", "digest": "f678485dc442d1cf", "bytes_per_launch": 12
 # the same source digest: the move kernel's bound is the L1's line-access
 # rate, set by its divergent 16-byte loads of the cells' planes and
 # neighbour codes.
-L1 = {"kernel": "move", "digest": "f678485dc442d1cf", "accesses_per_launch": 302200000,
+L1 = {"kernel": "move", "digest": "337bfdfe9033f966", "accesses_per_launch": 301600000,
       "workload": "cavity_40^3x6_Kn0.1", "source": "profiles/step_kernels_cavity40.md"}
 
 

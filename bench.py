@@ -62,7 +62,7 @@ L1 = {"kernel": "move", "digest": "fd67a97d0dfa22b5", "accesses_per_launch": 301
 
 def _kernel_digest():
     h = hashlib.sha256()
-    for f in ["kernels.hip", "collide.hip", "walls.hip", "device_common.h", "kernels.h"]:
+    for f in ["kernels.hip", "collide.hip", "slots.h", "walls.hip", "device_common.h", "kernels.h"]:
         h.update(open(os.path.join(ROOT, "paper_2607_08195_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

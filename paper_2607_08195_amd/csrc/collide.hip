@@ -4,6 +4,7 @@
 #include <algorithm>
 
 #include "kernels.h"
+#include "slots.h"
 
 namespace dsmcx {
 
@@ -448,19 +449,6 @@ __device__ __forceinline__ void load_info(CellInfo& f, int c, const CollideParam
     }
 }
 
-// Sum of v over the lanes below (one wave); *total over all.
-__device__ __forceinline__ int lanes_excl(int v, int* total) {
-    const int lane = threadIdx.x & 63;
-    int incl = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += t;
-    }
-    *total = __shfl(incl, 63, 64);
-    return incl - v;
-}
-
 // Collisions of the cells of a window (lane l of every wave: cell l, `live`
 // when it is one of them, its N particles in cv from s0), then their sums.
 // Candidate pairs are taken in rounds of at most kPairSlots: drawn one per
@@ -492,17 +480,10 @@ __device__ __forceinline__ void collide_cells(const Acc& cv, bool live, int s0, 
         }
 #pragma unroll 1
         for (int kb = 0;;) {
-            int m = left, base = 0;
+            int m = 0, base = 0;
             if (wave == 0) {
-                // all candidates that are left when they fit in the slots,
-                // else the same number from each cell that has any
                 int total;
-                base = lanes_excl(m, &total);
-                if (total > kPairSlots) {
-                    const int most = kPairSlots / __popcll(__ballot(left > 0));
-                    m = left < most ? left : most;
-                    base = lanes_excl(m, &total);
-                }
+                m = share_slots<kPairSlots>(left, &base, &total);
                 if (lane < Slots::kCells) {
                     ps.first[lane] = base;
                     ps.base[lane] = kb - base;

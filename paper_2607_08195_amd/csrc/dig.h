@@ -44,10 +44,12 @@ struct DigCase {
 // Quotients by one divisor: its reciprocal once (correctly rounded), then per
 // quotient one correction by the exact remainder, which leaves it within
 // 1 + 2^-51 of half an ulp: it is the division's result but for one quotient in
-// about 2^51 (none in 4e8 random ones), as long as the remainder does not
-// underflow, which takes quotients of 1e-290.  Four instructions instead of
-// eleven, one of them at a quarter of the rate.  Zeros, infinities and NaN go
-// through the hardware's fix-up.
+// about 2^51 (none in 4e8 random ones).  Four instructions instead of eleven,
+// one of them at a quarter of the rate.  Zeros, infinities and NaN go through
+// the hardware's fix-up.  Its range: dividends of 2^-966 (1e-291) and more, as
+// below the remainder is not exact (there within an ulp of the division's
+// result); divisors over 2^-1024 (5.6e-309), whose reciprocal does not overflow;
+// quotients that do not overflow (NaN where the division gives infinity).
 struct Divisor {
     double b = 1.0, r = 1.0;
     Divisor() = default;

@@ -104,18 +104,21 @@ template <int NV>
 __device__ __forceinline__ bool prim_of(const DigGeom& g, const double* U, double* P) {
     if (!(U[0] > 0)) return false;
     P[0] = U[0];
-    const Divisor rho(U[0]);
-    P[1] = rho.of(U[1]);
-    P[2] = rho.of(U[2]);
-    P[3] = rho.of(U[3]);
+    // a density close to zero: both sides of the quotients into Divisor's range
+    const double up = U[0] < 0x1p-800 ? 0x1p+200 : 1.0;
+    const Divisor rho(up * U[0]);
+    P[1] = rho.of(up * U[1]);
+    P[2] = rho.of(up * U[2]);
+    P[3] = rho.of(up * U[3]);
+    const double e = rho.of(up * U[4]);
     const double uu = P[1] * P[1] + P[2] * P[2] + P[3] * P[3];
     if constexpr (NV == 6) {
-        const double er = rho.of(U[5]);
-        P[4] = g.cv.of((rho.of(U[4]) - 0.5 * uu) - er);
+        const double er = rho.of(up * U[5]);
+        P[4] = g.cv.of((e - 0.5 * uu) - er);
         P[5] = er / ((0.5 * g.dr) * g.R);
         return P[4] > 0 && isfinite(P[4]) && P[5] > 0 && isfinite(P[5]);
     }
-    P[4] = g.cv.of(rho.of(U[4]) - 0.5 * uu);
+    P[4] = g.cv.of(e - 0.5 * uu);
     return P[4] > 0 && isfinite(P[4]);
 }
 
@@ -224,8 +227,9 @@ __device__ __forceinline__ void add_viscous(const double* vis, const double* n, 
     }
 }
 
+// (Divided as it stands: near a vacuum the rate overflows, to a step of zero.)
 template <int NV>
-__device__ __forceinline__ double viscous_rate(const DigGeom& g, double T, double rho, const Divisor& dl) {
+__device__ __forceinline__ double viscous_rate(const DigGeom& g, double T, double rho, double dl) {
     const double mu = mu_of(g, T);
     if constexpr (NV == 6) {
         double kt, kr;
@@ -234,10 +238,10 @@ __device__ __forceinline__ double viscous_rate(const DigGeom& g, double T, doubl
         const double dt_ = kt / (1.5 * rho * g.R), dr_ = kr / ((0.5 * g.dr) * rho * g.R);
         if (dt_ > d) d = dt_;
         if (dr_ > d) d = dr_;
-        return dl.of(2.0 * d);
+        return 2.0 * d / dl;
     }
     const double dmom = 4.0 * mu / (3.0 * rho), dth = kappa_of(g, mu) / (1.5 * rho * g.R);
-    return dl.of(2.0 * (dmom > dth ? dmom : dth));
+    return 2.0 * (dmom > dth ? dmom : dth) / dl;
 }
 
 // Rotational relaxation source of rho e_r (eq. macro):
@@ -859,7 +863,7 @@ __global__ __launch_bounds__(kDigThreads, NV == 6 ? 2 : 3) void k_dig_residual(D
             for (int k = 0; k < NH; ++k) vis[k] += hf[k];
             const double uf[3] = {0.5 * (Pc[1] + Pn[1]), 0.5 * (Pc[2] + Pn[2]), 0.5 * (Pc[3] + Pn[3])};
             add_viscous<NV>(vis, n, uf, F);
-            if constexpr (FIRST) lamv = viscous_rate<NV>(g, Tf, rf, dl);
+            if constexpr (FIRST) lamv = viscous_rate<NV>(g, Tf, rf, dl.b);
         } else if (kind == kLinkWall || kind == kLinkSpecular) {
             const double p = Pc[0] * g.R * Pc[4];
 #pragma unroll
@@ -878,7 +882,7 @@ __global__ __launch_bounds__(kDigThreads, NV == 6 ? 2 : 3) void k_dig_residual(D
 #pragma unroll
                 for (int k = 0; k < NH; ++k) vis[k] += hf[k];
                 add_viscous<NV>(vis, n, gr.u, F);
-                if constexpr (FIRST) lamv = viscous_rate<NV>(g, gr.T, Pc[0], dl);
+                if constexpr (FIRST) lamv = viscous_rate<NV>(g, gr.T, Pc[0], dl.b);
             }
         } else if (kind == kLinkInflow) {
             const DigGroup& gr = g.groups[idx];

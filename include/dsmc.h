@@ -420,7 +420,9 @@ dsmc_status dsmc_graph_step(dsmc_ctx ctx, int32_t n_steps);
  * size, 0 as 2 but refused for a rotating gas and the deferred sort;
  * sort 0 scatter, 1 (default) gather, done by the collide kernel chunk by chunk
  * (by a kernel of its own with collide 0 or where no collide follows), 2 as 1
- * but refused for a rotating gas, 3 deferred.  The autotuner's sort_ms includes the collide kernel.
+ * but refused for a rotating gas, 3 deferred.  The autotuner's collide_ms
+ * includes the sort's kernels (permutation and gather) and its sort_ms the whole
+ * step but for the inflow.
  * Every schedule gives the same results.  A batch accepts only move 0-2
  * and 4-7, 12-17. */
 typedef struct {

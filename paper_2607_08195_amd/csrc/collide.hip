@@ -2,6 +2,7 @@
 // pair selection and collisions in each cell; eq. dsmc_temperatures for the
 // sums), with the launch wrapper that picks the kernel's instance.
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.h"
 #include "slots.h"
@@ -74,6 +75,13 @@ struct Stored {
 };
 
 constexpr int kStageBatch = 8;  // particles per lane loaded together
+// Particles from which a cell's ids are ranked by all lanes of the workgroup
+// instead of the few that are the cell's.  These make a pass over the N ids per
+// 48 or 64 of them, the workgroup one per 1,024, but cell after cell, up to
+// some 3,000 ids a window: as much as N^2 / 64 at this N.  Six FP32 cells of
+// 2,000 particles: 3.7 ms a step against 27.1 with their own lanes alone, of
+// 1,000 1.13 against 4.18, of 500 0.46 against 0.87; of 400 0.34 either way.
+constexpr int kRankAll = 448;
 
 // r[t] += o < p[t] for four ids.  Written out because a compare's lane mask
 // may not be read by the next two instructions: interleaved by four, none of
@@ -669,36 +677,47 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
         }
         __syncthreads();
         {
-            // logical order: lane q of a cell's kLanes ranks the ids q, q +
-            // kLanes, ..., kBatch of them against one pass over the cell
-            constexpr int kLanes = kCollideLanes / CC, kBatch = kLanes == 4 ? 12 : kLanes == 8 ? 8 : 4;
-            const int q = tid & (kLanes - 1), lc = tid / kLanes;
-            const bool mine = lc >= k0 && lc < k1;
-            const int s0 = mine ? soff[lc] - w0 : 0;
-            const int N = mine ? soff[lc + 1] - soff[lc] : 0;
-            for (int b0 = q; b0 < N; b0 += kLanes * kBatch) {
-                uint32_t pk[kBatch];
-                int r[kBatch];
+            // logical order: lane q of a cell's `lanes` ranks the ids q, q +
+            // lanes, ..., `batch` of them against one pass over the cell
+            auto rank = [&](int lc, int N, int q, auto lanes, auto batch) {
+                constexpr int L = decltype(lanes)::value, B = decltype(batch)::value;
+                const int s0 = soff[lc] - w0;
+                for (int b0 = q; b0 < N; b0 += L * B) {
+                    uint32_t pk[B];
+                    int r[B];
 #pragma unroll
-                for (int t = 0; t < kBatch; ++t) {
-                    const int x = b0 + kLanes * t;
-                    pk[t] = x < N ? u.ids[s0 + x] : 0u;
-                    r[t] = s0;
-                }
+                    for (int t = 0; t < B; ++t) {
+                        const int x = b0 + L * t;
+                        pk[t] = x < N ? u.ids[s0 + x] : 0u;
+                        r[t] = s0;
+                    }
 #pragma unroll 4
-                for (int x = 0; x < N; ++x) {
-                    const uint32_t o = u.ids[s0 + x];
+                    for (int x = 0; x < N; ++x) {
+                        const uint32_t o = u.ids[s0 + x];
 #pragma unroll
-                    for (int t = 0; t < kBatch; t += 4) rank4(o, pk + t, r + t);
-                }
+                        for (int t = 0; t < B; t += 4) rank4(o, pk + t, r + t);
+                    }
 #pragma unroll
-                for (int t = 0; t < kBatch; ++t) {
-                    const int x = b0 + kLanes * t;
-                    if (x < N) {
-                        ord[r[t]] = (uint16_t)(3 * (s0 + x));
-                        if (FUSED) p.cell[base + s0 + x] = c0 + lc;
+                    for (int t = 0; t < B; ++t) {
+                        const int x = b0 + L * t;
+                        if (x < N) {
+                            ord[r[t]] = (uint16_t)(3 * (s0 + x));
+                            if (FUSED) p.cell[base + s0 + x] = c0 + lc;
+                        }
                     }
                 }
+            };
+            constexpr int kLanes = kCollideLanes / CC, kBatch = kLanes == 4 ? 12 : kLanes == 8 ? 8 : 4;
+            const int lc = tid / kLanes;
+            const int N = lc >= k0 && lc < k1 ? soff[lc + 1] - soff[lc] : 0;
+            rank(lc, N <= kRankAll ? N : 0, tid & (kLanes - 1), std::integral_constant<int, kLanes>{},
+                 std::integral_constant<int, kBatch>{});
+            // the large cells by all lanes, one after another
+            const int n = lane >= k0 && lane < k1 ? soff[min(lane, CC - 1) + 1] - soff[min(lane, CC - 1)] : 0;
+            for (uint64_t big = __ballot(n > kRankAll); big; big &= big - 1) {
+                const int k = __builtin_ctzll(big);
+                rank(k, soff[k + 1] - soff[k], tid, std::integral_constant<int, kCollideLanes>{},
+                     std::integral_constant<int, 4>{});
             }
         }
         __syncthreads();

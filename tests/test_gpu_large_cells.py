@@ -1,0 +1,87 @@
+"""Cells of many particles: where the whole workgroup ranks a cell's ids instead
+of the cell's own few lanes, against the oracle; and the time of such cells.
+
+Criteria of test_gpu_collide (pair counts bit-exact, velocities within 1 float32
+ulp or 1e-12, sums within 1e-12)."""
+import time
+
+import numpy as np
+import pytest
+
+from oracle import Oracle
+from paper_2607_08195_amd import workloads as W
+from parity_util import compare_particles, compare_sums
+
+pytestmark = pytest.mark.gpu
+
+GASES = {"argon": W.Species(), "nitrogen": W.Species(mass=4.65e-26, omega=0.74, dof_rot=2, z_rot=2.59)}
+
+
+@pytest.fixture(scope="module")
+def D():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2607_08195_amd import dsmc
+    return dsmc
+
+
+# around the line (448) and around the ids that the workgroup ranks in one pass
+# (1,024); as single cells among small ones, next to each other, and first and
+# last of a workgroup's cells
+COUNTS = {0: 448, 1: 449, 2: 447, 15: 1024, 16: 1025, 33: 900, 34: 0, 35: 460, 63: 1023, 64: 1200, 65: 600, 66: 600}
+
+
+@pytest.mark.parametrize("n_hex,sort,vel_fp32,gas", [
+    (5, 1, 1, "argon"), (5, 3, 0, "argon"), (5, 0, 1, "nitrogen"), (5, 1, 0, "nitrogen"),
+    (18, 1, 1, "argon"), (18, 3, 1, "nitrogen"), (18, 0, 0, "argon")])
+def test_ranked_by_the_workgroup(D, n_hex, sort, vel_fp32, gas):
+    wl = W.cavity(n_hex=n_hex, Kn=0.1, ppc=20, vel_fp32=vel_fp32, n_ss=0, species=GASES[gas])
+    wl.run.dt *= 0.02  # the large cells' candidates grow with the square of their particles
+    m, rng = wl.mesh, np.random.default_rng(11)
+    counts = rng.integers(0, 6, m.n_tets)
+    for c, n in COUNTS.items():
+        counts[c] = n
+    counts[-1] = 500
+    cell = np.repeat(np.arange(m.n_tets), counts).astype(np.int32)
+    b = rng.exponential(1.0, (len(cell), 4))
+    b /= b.sum(axis=1, keepdims=True)
+    x = np.einsum("ij,ijk->ik", b, m.xyz[m.tets[cell]])
+    v = rng.normal(0.0, np.sqrt(W.KB * wl.run.T0 / wl.species.mass), (len(cell), 3))
+    if vel_fp32:
+        v = v.astype(np.float32).astype(np.float64)
+    pid = rng.permutation(len(cell)).astype(np.uint32)
+    ir = rng.exponential(W.KB * wl.run.T0, len(cell)) if wl.species.dof_rot else None
+    o = Oracle(wl)  # (its initial (sigma c)_max)
+    o.set_particles(x, v, cell, pid, 3, len(pid), ir=ir)
+    g = D.Simulation(wl, fill=False, capacity=2 * len(pid))
+    g.set_state(x, v, cell, pid, 3, len(pid), o.smax(), ir=ir)
+    g.set_tuning(15, 3, sort)
+    for _ in range(2):
+        o.step_stages(4 | 8 | 16)
+        g.step_stages(4 | 8 | 16)
+    (gc, ga), (oc, oa) = g.pair_counts(), o.pair_counts()
+    assert np.array_equal(gc, oc) and np.array_equal(ga, oa)
+    compare_particles(g.state(), o.particles(), vel_fp32)
+    compare_sums(g.sums(D.SAMPLE_STEADY)[0], o.sums(0))
+    g.close()
+
+
+def test_time_of_staged_cells(D):
+    """Six cells of 2,000 particles fit the stage with FP32 velocities and
+    exceed it with FP64 ones (then worked on in the particle store): staging
+    them is not the slower way."""
+    best = {}
+    sims = {f: D.Simulation(W.cavity(n_hex=1, Kn=1.0, ppc=2000, vel_fp32=f, n_ss=0)) for f in (1, 0)}
+    for _ in range(5):
+        for f, g in sims.items():
+            g.step(1)
+            g.sync()
+            t = time.perf_counter()
+            g.step(4)
+            g.sync()
+            best[f] = min(best.get(f, 1e9), time.perf_counter() - t)
+    print(f"FP32 {best[1] / 4e-3:.2f} ms a step, FP64 {best[0] / 4e-3:.2f}")
+    assert best[1] <= 1.3 * best[0], best
+    for g in sims.values():
+        g.close()

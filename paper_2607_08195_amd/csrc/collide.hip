@@ -793,12 +793,19 @@ template <class VT, bool VSS, bool ROT>
 static void launch_collide_v(hipStream_t s, PartDev<VT> p, const int32_t* offsets, const CollideParams& cp,
                              const Scalars* sc, int32_t* perm, int do_collide, int do_sample, int variant, int gmode,
                              PartDev<VT> src, const int32_t* sortperm, int64_t np) {
+    const int64_t need = np * 64 * 12 / (11 * (int64_t)std::max(cp.nt, 1));
     // Cells per workgroup: 64, a lane of the deciding wave each, keep that
     // wave full; where they would give the device's 256 CUs fewer than two
     // workgroups each, 16 (1,296 cells, FP64: 20.0 against 24.5 us; 24,500
     // cells, VSS: 104 against 130 us; but 73,000 cells of nitrogen 194
-    // against 133 us, 384,000 of argon 707 against 281 us).
-    if (variant == kCollideG3k && cp.nt <= 64 * 512) {
+    // against 133 us, 384,000 of argon 707 against 281 us).  Also 16 where 64
+    // cells' particles exceed even the largest stage: in windows of a few
+    // cells most lanes of the deciding waves idle, and three of these waves a
+    // CU decide more than two (35,000 cells, FP32, a step: 100 particles a
+    // cell 0.49 against 0.63 ms, 450 5.2 against 10.3; FP64 450 7.4 against
+    // 16.9; 83,000 cells of 90 0.97 against 1.09; of 60, which fit, 0.68
+    // against 0.62).
+    if ((variant == kCollideG3k && cp.nt <= 64 * 512) || need > collide_cap<VT, 64, VSS, ROT>(2, gmode)) {
         launch_collide_g<VT, 16, 3, VSS, ROT>(s, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src, sortperm);
         return;
     }
@@ -807,10 +814,11 @@ static void launch_collide_v(hipStream_t s, PartDev<VT> p, const int32_t* offset
     // more takes its cells in several windows): the waves wait at barriers
     // for a good half of their time, so more of them are worth more than
     // spare room (11.52M particles, 384,000 cells: 281 us with four, 318 with
-    // three, 415 with two).  The schedules other than the default fix it.  Four stages of FP64 velocities or rotational energies
-    // would hold a dozen particles a cell.
+    // three, 415 with two).  The schedules other than the default fix it.
+    // FP64 velocities or rotational energies: three at most (four stages would
+    // hold a dozen particles a cell, and the registers of four spill: 384,000
+    // cells of 12 FP64 particles 659 us a step against 624).
     constexpr int kMost = sizeof(VT) == 4 && !ROT ? 4 : 3;
-    const int64_t need = np * 64 * 12 / (11 * (int64_t)std::max(cp.nt, 1));
     int wg = 2;
     if (variant == kCollideGlobal8 || variant == kCollideLds) wg = 3;
     else if (variant == kCollideG2k) wg = kMost;

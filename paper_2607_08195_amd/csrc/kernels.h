@@ -26,7 +26,8 @@ enum { kMoveLane = 0, kMoveLaneW6 = 1, kMoveLaneW8 = 2, kMoveBatched = 3, kMoveD
        kMoveFace3 = 15, kMoveFace3W8 = 16, kMovePersist = 17 };
 // collide schedules: workgroups per CU (0 and 2: three, 1: two, 4: four, or
 // three where the stage would be too small; 3, the default: by occupancy and
-// mesh size)
+// mesh size).  All of them take 16-cell workgroups where the particles of 64
+// cells exceed the largest stage.
 enum { kCollideLds = 0, kCollideGlobal = 1, kCollideGlobal8 = 2, kCollideG3k = 3, kCollideG2k = 4 };
 // sort: scatter by rank; gather and fused (k_perm, then the collide kernel
 // gathers each chunk as it stages it: 11.52M particles, 1,330 us a step against

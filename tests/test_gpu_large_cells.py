@@ -26,23 +26,10 @@ def D():
     return dsmc
 
 
-# around the line (448) and around the ids that the workgroup ranks in one pass
-# (1,024); as single cells among small ones, next to each other, and first and
-# last of a workgroup's cells
-COUNTS = {0: 448, 1: 449, 2: 447, 15: 1024, 16: 1025, 33: 900, 34: 0, 35: 460, 63: 1023, 64: 1200, 65: 600, 66: 600}
-
-
-@pytest.mark.parametrize("n_hex,sort,vel_fp32,gas", [
-    (5, 1, 1, "argon"), (5, 3, 0, "argon"), (5, 0, 1, "nitrogen"), (5, 1, 0, "nitrogen"),
-    (18, 1, 1, "argon"), (18, 3, 1, "nitrogen"), (18, 0, 0, "argon")])
-def test_ranked_by_the_workgroup(D, n_hex, sort, vel_fp32, gas):
-    wl = W.cavity(n_hex=n_hex, Kn=0.1, ppc=20, vel_fp32=vel_fp32, n_ss=0, species=GASES[gas])
-    wl.run.dt *= 0.02  # the large cells' candidates grow with the square of their particles
-    m, rng = wl.mesh, np.random.default_rng(11)
-    counts = rng.integers(0, 6, m.n_tets)
-    for c, n in COUNTS.items():
-        counts[c] = n
-    counts[-1] = 500
+def _matches_oracle(D, wl, counts, sort, steps):
+    """Particles of the cells' given counts (uniform in the cell, Maxwellian, ids
+    shuffled) through sort, collisions and sampling."""
+    m, rng, vel_fp32 = wl.mesh, np.random.default_rng(11), wl.run.vel_fp32
     cell = np.repeat(np.arange(m.n_tets), counts).astype(np.int32)
     b = rng.exponential(1.0, (len(cell), 4))
     b /= b.sum(axis=1, keepdims=True)
@@ -57,7 +44,7 @@ def test_ranked_by_the_workgroup(D, n_hex, sort, vel_fp32, gas):
     g = D.Simulation(wl, fill=False, capacity=2 * len(pid))
     g.set_state(x, v, cell, pid, 3, len(pid), o.smax(), ir=ir)
     g.set_tuning(15, 3, sort)
-    for _ in range(2):
+    for _ in range(steps):
         o.step_stages(4 | 8 | 16)
         g.step_stages(4 | 8 | 16)
     (gc, ga), (oc, oa) = g.pair_counts(), o.pair_counts()
@@ -65,6 +52,34 @@ def test_ranked_by_the_workgroup(D, n_hex, sort, vel_fp32, gas):
     compare_particles(g.state(), o.particles(), vel_fp32)
     compare_sums(g.sums(D.SAMPLE_STEADY)[0], o.sums(0))
     g.close()
+
+
+# around the line (448) and around the ids that the workgroup ranks in one pass
+# (1,024); as single cells among small ones, next to each other, and first and
+# last of a workgroup's cells
+COUNTS = {0: 448, 1: 449, 2: 447, 15: 1024, 16: 1025, 33: 900, 34: 0, 35: 460, 63: 1023, 64: 1200, 65: 600, 66: 600}
+
+
+@pytest.mark.parametrize("n_hex,sort,vel_fp32,gas", [
+    (5, 1, 1, "argon"), (5, 3, 0, "argon"), (5, 0, 1, "nitrogen"), (5, 1, 0, "nitrogen"),
+    (18, 1, 1, "argon"), (18, 3, 1, "nitrogen"), (18, 0, 0, "argon")])
+def test_ranked_by_the_workgroup(D, n_hex, sort, vel_fp32, gas):
+    wl = W.cavity(n_hex=n_hex, Kn=0.1, ppc=20, vel_fp32=vel_fp32, n_ss=0, species=GASES[gas])
+    wl.run.dt *= 0.02  # the large cells' candidates grow with the square of their particles
+    counts = np.random.default_rng(12).integers(0, 6, wl.mesh.n_tets)
+    for c, n in COUNTS.items():
+        counts[c] = n
+    counts[-1] = 500
+    _matches_oracle(D, wl, counts, sort, 2)
+
+
+@pytest.mark.parametrize("sort,vel_fp32,gas", [(1, 1, "argon"), (3, 1, "argon"), (1, 0, "nitrogen")])
+def test_dense_mesh(D, sort, vel_fp32, gas):
+    """34,992 cells whose particles exceed the largest stage 64 cells at a time:
+    the workgroups take 16 cells, as on a small mesh."""
+    wl = W.cavity(n_hex=18, Kn=0.1, ppc=20, vel_fp32=vel_fp32, n_ss=0, species=GASES[gas])
+    wl.run.dt *= 0.1
+    _matches_oracle(D, wl, np.random.default_rng(13).integers(50, 130, wl.mesh.n_tets), sort, 1)
 
 
 def test_time_of_staged_cells(D):
@@ -83,5 +98,25 @@ def test_time_of_staged_cells(D):
             best[f] = min(best.get(f, 1e9), time.perf_counter() - t)
     print(f"FP32 {best[1] / 4e-3:.2f} ms a step, FP64 {best[0] / 4e-3:.2f}")
     assert best[1] <= 1.3 * best[0], best
+    for g in sims.values():
+        g.close()
+
+
+def test_time_of_dense_mesh(D):
+    """A step of 34,992 cells takes 2.1 times that of 16,464 at the same 450
+    particles a cell, within 40 %: the larger mesh's workgroups do not wait for
+    one cell after another."""
+    best = {}
+    sims = {n: D.Simulation(W.cavity(n_hex=n, Kn=0.1, ppc=450, vel_fp32=0, n_ss=0)) for n in (14, 18)}
+    for _ in range(4):
+        for n, g in sims.items():
+            g.step(1)
+            g.sync()
+            t = time.perf_counter()
+            g.step(3)
+            g.sync()
+            best[n] = min(best.get(n, 1e9), time.perf_counter() - t)
+    print(f"16,464 cells {best[14] / 3e-3:.2f} ms a step, 34,992 {best[18] / 3e-3:.2f}")
+    assert best[18] <= 1.4 * (18 / 14) ** 3 * best[14], best
     for g in sims.values():
         g.close()

@@ -235,6 +235,12 @@ __host__ __device__ constexpr int kNkCs(int m) { return m * (m + 1); }
 __host__ __device__ constexpr int kNkSn(int m) { return m * (m + 2); }
 __host__ __device__ constexpr int kNkGv(int m) { return m * (m + 3); }
 __host__ __device__ constexpr int kNkGmSize(int m) { return m * (m + 4) + 1; }
+// Blocks up to which the kernel that normalises a basis vector adds their
+// partial sums itself, in every one of its blocks, instead of a launch before it
+// (us, in the kernel against apart, without the gap between the two: 768 blocks
+// 11.7 against 8.0 + 4.7, 1,500 22.4 against 16.3 + 4.8, 2,930 49.6 against
+// 29.0 + 5.4, 12,000 351 against 113 + 18: its loads grow with their square).
+constexpr int kNkFoldBlocks = 1536;
 constexpr int kNkAhead = 2;     // GMRES steps in the stream at a time
 constexpr int kNkHostSlot = 4;  // doubles
 // Residual and spectral sums at w.prim (w.Rs, w.dt = V / S), the stopping

@@ -1571,7 +1571,8 @@ void launch_aa_update(hipStream_t s, const DigGeom& g, const AaWork& a, int cnt,
 // reduced in a fixed order: wave, then the block's four waves, then over the
 // blocks: k_nk_reduce for the many columns of a Gram-Schmidt pass, the next
 // kernel's own blocks for one or two (nk_fold; for many it measured 107 us a
-// GMRES step against 98 on 63,888 cells, and no gain on 6,000).
+// GMRES step against 98 on 63,888 cells, and no gain on 6,000), if there are
+// few enough of them (kNkFoldBlocks).
 //
 // The device carries the GMRES cycle by itself (k_nk_step: rotations, residual,
 // stop), so that the host launches ahead of it: with a host round trip per
@@ -1940,18 +1941,20 @@ __global__ __launch_bounds__(kDigThreads) void k_nk_orth(DigGeom g, const DigCtl
     nk_block_store(red, j + 1, nk.part);
 }
 
-// V_{j+1} = w / |w| (when |w| > 0), |w|^2 from its block partials `in`;
-// partial of |V_{j+1} / p|^2 into `part`.
-template <int NV>
+// V_{j+1} = w / |w| (when |w| > 0), |w|^2 from its block partials `in` (FOLD) or
+// reduced before; partial of |V_{j+1} / p|^2 into `part`.
+template <int NV, bool FOLD>
 __global__ __launch_bounds__(kDigThreads) void k_nk_normalize(DigGeom g, DigWork w, NkWork nk, int j, double cfl,
                                                               const double* in, double* part) {
     if (stopped(w.ctl)) return;
     __shared__ double red[1][kDigThreads / 64], hn2;
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     double q2 = 0.0;
-    nk_fold(in, gridDim.x, 1, &hn2);
-    if (blockIdx.x == 0 && threadIdx.x == 0) nk.red[kNkHn2(nk.m)] = hn2;
-    const double hn = sqrt(hn2);
+    if constexpr (FOLD) {
+        nk_fold(in, gridDim.x, 1, &hn2);
+        if (blockIdx.x == 0 && threadIdx.x == 0) nk.red[kNkHn2(nk.m)] = hn2;
+    }
+    const double hn = sqrt(FOLD ? hn2 : nk.red[kNkHn2(nk.m)]);
     if (c < g.nt && hn > 0) {
         const size_t n = (size_t)NV * g.nt;
         const double pc = g.vol[c] / w.dt[c] * (1.0 + 1.0 / cfl);
@@ -2065,7 +2068,11 @@ void launch_nk_arnoldi(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, Nk
     hipLaunchKernelGGL(DIG_NV(g, k_nk_orth), gr, bl, 0, s, g, ctl, nk, j, kNkH1(m), 0);
     hipLaunchKernelGGL(k_nk_reduce, dim3(j + 1), bl, 0, s, ctl, (const double*)A, nblk, nk.red + kNkH2(m));
     hipLaunchKernelGGL(DIG_NV(g, k_nk_orth), gr, bl, 0, s, g, ctl, nk, j, kNkH2(m), 1);
-    hipLaunchKernelGGL(DIG_NV(g, k_nk_normalize), gr, bl, 0, s, g, w, nk, j, cfl, (const double*)A, B);
+    const bool fold = nblk <= kNkFoldBlocks;
+    if (!fold) hipLaunchKernelGGL(k_nk_reduce, dim3(1), bl, 0, s, ctl, (const double*)A, nblk, nk.red + kNkHn2(m));
+    const auto normalize = g.dr ? (fold ? k_nk_normalize<kDigNVR, true> : k_nk_normalize<kDigNVR, false>)
+                                : (fold ? k_nk_normalize<kDigNV, true> : k_nk_normalize<kDigNV, false>);
+    hipLaunchKernelGGL(normalize, gr, bl, 0, s, g, w, nk, j, cfl, (const double*)A, B);
     hipLaunchKernelGGL(k_nk_step, dim3(1), bl, 0, s, (const double*)B, nblk, nk, w.ctl, j,
                        (double)(g.dr ? kDigNVR : kDigNV) * g.nt, fd, eta, nk.host + kNkHostSlot * (1 + j % kNkAhead));
 }

@@ -864,7 +864,7 @@ static int solve_nk(osim* s, double* prim, const double* hotf, const odig_params
     double* h = (double*)malloc(sizeof(double) * (m + 1));
     for (int c = 0; c < nt; ++c) cons_of(s, prim + nv * (size_t)c, U + nv * (size_t)c);
     double res0 = 0.0, res = 0.0, cfl = prm->cfl, bprev = 0.0, lin = 0.0;
-    int k = 0, conv = 0, failed = 0, nkry = 0;
+    int k = 0, conv = 0, failed = 0, nkry = 0, nhalf = 0;
     for (k = 0; k < prm->n_m; ++k) {
         gradients(s, prim, g);
         residual_all(s, prim, hotf, g, R0, spec);
@@ -995,10 +995,12 @@ static int solve_nk(osim* s, double* prim, const double* hotf, const odig_params
                 }
                 ok = prim_of(s, Ut + nv * (size_t)c, Pt + nv * (size_t)c);
             }
-            if (ok)
+            if (ok) {
                 accepted = 1;
-            else
+            } else {
                 alpha = 0.5 * alpha;
+                ++nhalf;
+            }
         }
         if (!accepted) {
             failed = 1;
@@ -1013,6 +1015,7 @@ static int solve_nk(osim* s, double* prim, const double* hotf, const odig_params
         rep->converged = conv;
         rep->failed = failed;
         rep->krylov_steps = nkry;
+        rep->halved = nhalf;
     }
     free(g); free(R0); free(Rp); free(spec); free(specp); free(pc); free(U); free(Ut); free(Pt); free(V);
     free(w); free(z); free(H); free(cs); free(sn); free(gv); free(y); free(h);

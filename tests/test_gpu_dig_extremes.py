@@ -53,3 +53,72 @@ def test_near_vacuum_matches_oracle(D, gas, rho):
         assert (a["iters"], a["failed"]) == (b["iters"], b["failed"]) == (n_m, 0)
         _states_close(pg, po, wl, 1e-10)
     g.close()
+
+
+def _noise(wl, nt, spread):
+    rng = np.random.default_rng(7)
+    nv = 6 if wl.species.dof_rot else 5
+    cs = np.sqrt(KB / wl.species.mass * wl.run.T0)
+    p0 = wl.run.n0 * KB * wl.run.T0
+    prim = np.empty((nt, nv))
+    prim[:, 0] = wl.species.mass * wl.run.n0 * (1 + spread * rng.random(nt))
+    prim[:, 1:4] = spread * cs * rng.standard_normal((nt, 3))
+    prim[:, 4:] = wl.run.T0 * (1 + spread * rng.random((nt, nv - 4)))
+    hot = 0.01 * p0 * rng.standard_normal((nt, 12 if nv == 6 else 9))
+    hot[:, 6:] *= cs
+    return prim, hot
+
+
+# Steps too long for the scheme, by the number of iterations that were
+# completed and the stage that then fails (as the oracle has it; each some way
+# from the CFL numbers where these change).
+FAILING = [  # gas, spread, one step for all cells, cfl, completed, failing stage
+    ("argon", 0.3, 0, 40.0, 0, 1), ("argon", 0.01, 0, 21.0, 1, 1), ("argon", 0.1, 0, 11.0, 1, 2),
+    ("argon", 0.1, 0, 9.25, 1, 3), ("argon", 0.1, 0, 7.75, 2, 3), ("argon", 0.1, 0, 6.875, 3, 3),
+    ("argon", 0.1, 1, 12.25, 1, 2), ("argon", 0.1, 1, 10.0, 1, 3), ("argon", 0.1, 1, 8.5, 2, 3),
+    ("nitrogen", 0.3, 0, 40.0, 0, 1), ("nitrogen", 0.01, 0, 23.5, 1, 1), ("nitrogen", 0.1, 0, 11.0, 1, 2),
+    ("nitrogen", 0.1, 0, 9.25, 1, 3), ("nitrogen", 0.1, 0, 7.5, 2, 3), ("nitrogen", 0.1, 1, 12.0, 1, 2),
+    ("nitrogen", 0.1, 1, 8.25, 2, 3)]
+
+
+@pytest.mark.parametrize("gas,spread,one,cfl,done,stage", FAILING)
+def test_failing_march_leaves_the_last_good_state(D, gas, spread, one, cfl, done, stage):
+    """A solve that fails in a first, second or third stage, after an even or an
+    odd number of iterations, in its last iteration or with others launched
+    behind it: the oracle's counts, its state within 1e-8 of the column's scale,
+    and bit for bit that of a solve of the completed iterations alone."""
+    wl = W.cavity(n_hex=3, Kn=0.1, ppc=4, vel_fp32=0, jitter=0.1, lid_speed=50.0, species=GASES[gas])
+    o, g = Oracle(wl), D.Simulation(wl)
+    prim, hot = _noise(wl, o.nt, spread)
+    kw = dict(eps_m=0.0, cfl=cfl, global_dt=one)
+    good = g.dig_solve(prim, hot, n_m=done, **kw)[0] if done else prim
+    for n_m in (done + 1, done + 2, 60):
+        pg, a = g.dig_solve(prim, hot, n_m=n_m, **kw)
+        po, b = o.dig_solve(prim, hot, n_m=n_m, **kw)
+        assert (a["iters"], a["failed"]) == (b["iters"], b["failed"]) == (done, 1)
+        assert np.all(np.abs(pg - po) <= 1e-8 * np.abs(po).max(axis=0, keepdims=True))
+        assert np.array_equal(pg, good)
+    g.close()
+
+
+@pytest.mark.parametrize("gas", ["argon", "nitrogen"])
+def test_halved_update_matches_oracle(D, gas):
+    """A Newton step whose update the oracle halves twice: the state within 1e-6
+    of the column's scale (the Newton-Krylov tests' tolerance)."""
+    wl = W.cavity(n_hex=4, Kn=0.1, ppc=2, lid_speed=50.0, jitter=0.1, species=GASES[gas])
+    o = Oracle(wl, fill=False)
+    o.set_reference(wl.run.n0, wl.run.T0)
+    g = D.Simulation(wl)
+    prim, hot = _noise(wl, o.nt, 0.01)
+    rng = np.random.default_rng(3)
+    prim[:, 0] *= 1 + 0.9 * (rng.random(o.nt) - 0.5) * 2
+    prim[:, 4:] *= 1 + 0.9 * (rng.random((o.nt, prim.shape[1] - 4)) - 0.5) * 2
+    kw = dict(n_m=1, eps_m=0.0, cfl=1e3, solver=1, krylov=20)
+    pg, a = g.dig_solve(prim, hot, **kw)
+    po, b = o.dig_solve(prim, hot, **kw)
+    assert b["halved"] > 0
+    assert [a[k] for k in ("iters", "failed", "krylov_steps")] == [b[k] for k in ("iters", "failed", "krylov_steps")]
+    scale = np.abs(po).max(axis=0, keepdims=True)
+    scale[:, 1:4] = np.abs(po[:, 1:4]).max()
+    assert np.all(np.abs(pg - po) <= 1e-6 * scale)
+    g.close()

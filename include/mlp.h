@@ -84,10 +84,10 @@ dsmc_status dsmc_mlp_backward(dsmc_mlp net, const float* x, const float* t, int6
  * DSMC_MLP_NOALLOC_MAX_ROWS (DSMC_E_INVALID otherwise).  The work is
  * enqueued on the network's stream and the call returns at once.  Its
  * per-block partials live in a fixed scratch array of the library
- * (DSMC_MLP_NOALLOC_MAX_ROWS / 32 blocks of 35,977 floats, 18.4 MB, held on
- * each device that creates a network until the process ends) shared by
- * every call on that device: calls that overlap on one device race, so the
- * caller orders them (one stream, or events).  Results equal
+ * (DSMC_MLP_NOALLOC_MAX_ROWS / 32 blocks of 35,980 floats, a gradient padded
+ * to 16 bytes, and a loss each: 18.4 MB, held on each device that creates a
+ * network until the process ends) shared by every call on that device: calls
+ * that overlap on one device race, so the caller orders them (one stream, or events).  Results equal
  * dsmc_mlp_backward's on the same rows. */
 #define DSMC_MLP_NOALLOC_MAX_ROWS 4096
 dsmc_status dsmc_mlp_backward_noalloc(dsmc_mlp net, const float* x, const float* t, int64_t rows, float* grad,

@@ -129,7 +129,8 @@ CollideParams collide_params(dsmc_ctx c) {
     return cp;
 }
 
-// The deferred sort needs the three-face move and an LDS-ranked collide.
+// The deferred sort needs the three-face move and a collide schedule that can do
+// the gather (one that reaches the particles through the sorted order).
 bool deferred_ok(int move, int collide) { return move == kMoveFace3 && collide_fuses_gather(collide); }
 
 }  // namespace
@@ -307,15 +308,18 @@ dsmc_status step_any(dsmc_ctx c, int mask) {
 
 // Schedules that carry the rotational energy of a rotating gas: the
 // parked-wall move kernels (their main pass stops at diffuse walls, whose
-// re-emission, rotation included, the walls pass makes), the LDS-ranked
-// collide kernels and the scatter or gather sort.
+// re-emission, rotation included, the walls pass makes), collide schedules 1-4
+// and the scatter, gather or deferred sort.  (The kernels would serve
+// schedule 0 too, and the fused sort is the gather sort by another name; both
+// stay refused for a rotating gas.)
 bool rot_schedule_ok(int move, int collide, int sort) {
     const bool mv = move == kMoveDefer4 || move == kMoveDefer5 || move == kMoveDefer6 || move == kMoveDefer8 ||
                     move == kMoveCap4 || move == kMoveCap5 || move == kMoveCap6 || move == kMoveFace3 ||
                     move == kMoveFace3W8 || move == kMovePersist;
-    const bool co = collide == kCollideGlobal || collide == kCollideGlobal8 || collide == kCollideG3k ||
-                    collide == kCollideG2k;
-    const bool so = sort == kSortScatter || sort == kSortGather || (sort == kSortDeferred && deferred_ok(move, collide));
+    const bool co = collide == kCollideWg2 || collide == kCollideWg3 || collide == kCollideAuto ||
+                    collide == kCollideWg4;
+    const bool so = sort == kSortScatter || sort == kSortGather ||
+                    (sort == kSortDeferred && deferred_ok(move, collide));
     return mv && co && so;
 }
 
@@ -329,7 +333,8 @@ bool move_reads_cases(int v) {
 
 // Tuning overrides from the environment: DSMC_MOVE (lane, lane6, lane8,
 // batched, defer4/5/6/8, face3, face3w8, cap4/5/6, refill5/6, pool128/256), DSMC_MOVE_BATCH,
-// DSMC_REORDER (0/1), DSMC_SORT, DSMC_COLLIDE.
+// DSMC_REORDER (0/1), DSMC_SORT, DSMC_COLLIDE (lds, global, global8, global3k,
+// global2k: schedules 0 to 4 by the names of their first kernels).
 void read_tuning(dsmc_ctx c) {
     if (const char* v = std::getenv("DSMC_MOVE")) {
         std::string s(v);
@@ -364,11 +369,11 @@ void read_tuning(dsmc_ctx c) {
     }
     if (const char* v = std::getenv("DSMC_COLLIDE")) {
         std::string s(v);
-        if (s == "lds") c->collide_variant = kCollideLds;
-        else if (s == "global") c->collide_variant = kCollideGlobal;
-        else if (s == "global8") c->collide_variant = kCollideGlobal8;
-        else if (s == "global3k") c->collide_variant = kCollideG3k;
-        else if (s == "global2k") c->collide_variant = kCollideG2k;
+        if (s == "lds") c->collide_variant = kCollideApart3;
+        else if (s == "global") c->collide_variant = kCollideWg2;
+        else if (s == "global8") c->collide_variant = kCollideWg3;
+        else if (s == "global3k") c->collide_variant = kCollideAuto;
+        else if (s == "global2k") c->collide_variant = kCollideWg4;
     }
 }
 
@@ -541,7 +546,7 @@ dsmc_status init_impl(dsmc_ctx* out, const dsmc_mesh_desc* mesh, const dsmc_spec
         // the rotating gas runs the kernels that carry the rotational energy
         if (!rot_schedule_ok(c->move_variant, c->collide_variant, c->sort_variant)) {
             c->move_variant = kMoveFace3;
-            c->collide_variant = kCollideG3k;
+            c->collide_variant = kCollideAuto;
             c->sort_variant = kSortGather;
         }
     }
@@ -884,14 +889,14 @@ dsmc_status dsmc_get_tuning(dsmc_ctx c, dsmc_tuning* t) {
 dsmc_status dsmc_set_tuning(dsmc_ctx c, const dsmc_tuning* t) {
     if (!c || !t) return fail(c, DSMC_E_INVALID, "bad arguments");
     const bool batch_ok = move_reads_cases(t->move);
-    if (t->move < 0 || t->move > kMovePersist || t->collide < 0 || t->collide > kCollideG2k || t->sort < 0 ||
+    if (t->move < 0 || t->move > kMovePersist || t->collide < 0 || t->collide > kCollideWg4 || t->sort < 0 ||
         t->sort > kSortDeferred || (c->n_cases && !batch_ok))
         return fail(c, DSMC_E_INVALID, "unknown or unsupported kernel variant");
     if (t->sort == kSortDeferred && !deferred_ok(t->move, t->collide))
-        return fail(c, DSMC_E_INVALID, "the deferred sort needs the three-face move and an LDS-ranked collide");
+        return fail(c, DSMC_E_INVALID, "the deferred sort needs the three-face move and a collide schedule of 1 to 4");
     if (c->dr && !rot_schedule_ok(t->move, t->collide, t->sort))
-        return fail(c, DSMC_E_INVALID, "a rotating gas needs a parked-wall move, LDS-ranked collide and scatter, "
-                                       "gather or deferred sort schedule");
+        return fail(c, DSMC_E_INVALID, "a rotating gas needs a parked-wall move, a collide schedule of 1 to 4 "
+                                       "and a scatter, gather or deferred sort schedule");
     if (t->sort != kSortDeferred) {
         dsmc_status st = materialize(c);
         if (st != DSMC_OK) return st;
@@ -927,7 +932,7 @@ dsmc_status dsmc_autotune(dsmc_ctx c, int32_t trial_steps, dsmc_tuning* out) {
         if (ms < best.move_ms) { best.move_ms = ms; best.move = v; }
     }
     c->move_variant = best.move;
-    const int collides[] = {kCollideGlobal, kCollideGlobal8, kCollideG3k, kCollideG2k, kCollideLds};
+    const int collides[] = {kCollideWg2, kCollideWg3, kCollideAuto, kCollideWg4, kCollideApart3};
     for (int v : collides) {
         if (c->dr && !rot_schedule_ok(c->move_variant, v, c->sort_variant)) continue;
         c->collide_variant = v;

@@ -532,27 +532,33 @@ constexpr int stage_cap(int wg) {
     return (4 * cap <= slots ? cap : std::max(slots / 4, room / (per + 4))) & ~31;
 }
 
-// A workgroup works on CC consecutive cells.  Per window of them
-// whose particles fit the stage (one window as a rule) the particles' ids
-// and velocities (rotational energies) are staged in LDS with one round of
-// coalesced loads, and four lanes a cell rank its ids; then the candidate
-// pairs, the collisions and the sums (collide_cells).  A single cell beyond
-// the stage works on the particle store through a global order table.
+// A workgroup works on CC consecutive cells.  Per window of them whose
+// particles fit the stage (one window as a rule) the particles' ids and
+// velocities (rotational energies) are staged in LDS with one round of
+// coalesced loads, and four lanes a cell (16 in workgroups of 16 cells, all of
+// them where the cell is large) rank its ids; then the candidate pairs, the
+// collisions and the sums (collide_cells).  A single cell beyond the stage
+// works on the particle store through a global order table.
 // With FUSED, the cells' slots of the sorted buffer p are filled from the
 // unsorted buffer src through the gather permutation (slot -> source index):
 // velocities and ids go through the stage, the rest passes through once the
-// window has been worked on, while other workgroups compute.  On the 40^3
-// cavity 474 us, against 367 for a gather of its own and 280 for this kernel
-// without (and 35 less in the permutation, which need not write the cells).
-// With IND (deferred sort) nothing is moved: slot d of the sorted order is
-// particle sortperm[d] of p.
-// Bound: VALU issue (16,700 wave instructions per 64 cells at 30 particles a
-// cell and Kn 0.1: a quarter the ranking, a quarter the candidates' draws, a
-// fifth each the decisions and the sums) at 54 % of it, the rest being the
-// waits for the one deciding wave.  On the 40^3 cavity 281 us (408 MB of HBM
-// traffic, 1.5 TB/s), against 360 us with one wave per 64 cells that drew,
-// decided and summed cell by cell, a lane each, at 47-63 % lane efficiency
-// and two waves per SIMD; nitrogen on 73,000 cells 133 against 209 us.
+// window has been worked on, while other workgroups compute.  With IND
+// (deferred sort) nothing is moved: slot d of the sorted order is particle
+// sortperm[d] of p.
+// On the 40^3 cavity (11.52M particles, Kn 0.1) FUSED takes 461 us, against 367
+// for a gather of its own and 281 for this kernel without (and 35 more in the
+// permutation, which then writes the cells).  Bound: its 2.2 GB of HBM traffic
+// at 4.7 TB/s (a copy reaches 5.2) and, beside it, the waits for the one
+// deciding wave.  Without the gather it moves 408 MB, and VALU issue (16,200
+// wave instructions per 64 cells: a quarter the ranking, a quarter the
+// candidates' draws, a fifth each the decisions and the sums; 159 us at full
+// issue) takes 54 % of its time, those waits the rest.  One wave per 64 cells
+// that drew, decided and summed cell by cell, a lane each, at 47-63 % lane
+// efficiency and two waves per SIMD, took 360 us; nitrogen on 73,000 cells 133
+// against 209 us.  With one to three particles a cell on hundreds of thousands
+// of cells that wave was the faster one (384,000 cells of one, nitrogen: 101
+// against 142 us): a workgroup's chain of phases is then all there is, and
+// fewer of them fit a CU.
 template <class VT, int CC, int WG, int GM, bool VSS, bool ROT>
 __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(WG))) void k_collide_sample(
     PartDev<VT> p, const int32_t* offsets, CollideParams cp, const Scalars* sc, int32_t* perm, int do_collide,
@@ -583,8 +589,8 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
     // Workgroups go round-robin over the 8 XCDs: eight consecutive ones of an
     // XCD take eight consecutive pieces of the cells, so that its L2 holds the
     // source lines that neighbouring cells' gathers share (40^3 cavity: 1.52 GB
-    // fetched against 2.15, 474 us against 486; one slice per XCD 501, and
-    // 132 against 107 on a mesh whose busy cells lie together).  gridDim.x is a
+    // fetched against 2.15, 2.5 % less time; one slice per XCD 3 % more, and
+    // 132 us against 107 on a mesh whose busy cells lie together).  gridDim.x is a
     // multiple of 64; the last workgroups may be past the last cell.
     const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
     const int c0 = ((seq >> 3) * 64 + xcd * 8 + (seq & 7)) * CC;
@@ -633,8 +639,8 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
             }
             __syncthreads();
             const Stored<VT> cv{p.vel, perm + base, p.ir};
-            collide_cells<VSS, ROT>(cv, lane == k0 && c < nt, 0, N, c, wave, *(StoredSlots*)lv, tab, cp, step, do_collide,
-                                    do_sample, f, sums);
+            collide_cells<VSS, ROT>(cv, lane == k0 && c < nt, 0, N, c, wave, *(StoredSlots*)lv, tab, cp, step,
+                                    do_collide, do_sample, f, sums);
             ++k0;
             __syncthreads();
             continue;
@@ -768,7 +774,7 @@ static int collide_cap(int wg, int gmode) {
                                     : stage_cap<VT, CC, false, VSS, ROT>(wg);
 }
 
-bool collide_fuses_gather(int variant) { return variant != kCollideLds; }
+bool collide_fuses_gather(int variant) { return variant != kCollideApart3; }
 
 template <class VT, int CC, int WG, bool VSS, bool ROT>
 static void launch_collide_g(hipStream_t s, PartDev<VT> p, const int32_t* offsets, const CollideParams& cp,
@@ -805,7 +811,7 @@ static void launch_collide_v(hipStream_t s, PartDev<VT> p, const int32_t* offset
     // cell 0.49 against 0.63 ms, 450 5.2 against 10.3; FP64 450 7.4 against
     // 16.9; 83,000 cells of 90 0.97 against 1.09; of 60, which fit, 0.68
     // against 0.62).
-    if ((variant == kCollideG3k && cp.nt <= 64 * 512) || need > collide_cap<VT, 64, VSS, ROT>(2, gmode)) {
+    if ((variant == kCollideAuto && cp.nt <= 64 * 512) || need > collide_cap<VT, 64, VSS, ROT>(2, gmode)) {
         launch_collide_g<VT, 16, 3, VSS, ROT>(s, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src, sortperm);
         return;
     }
@@ -820,9 +826,9 @@ static void launch_collide_v(hipStream_t s, PartDev<VT> p, const int32_t* offset
     // cells of 12 FP64 particles 659 us a step against 624).
     constexpr int kMost = sizeof(VT) == 4 && !ROT ? 4 : 3;
     int wg = 2;
-    if (variant == kCollideGlobal8 || variant == kCollideLds) wg = 3;
-    else if (variant == kCollideG2k) wg = kMost;
-    else if (variant != kCollideGlobal)
+    if (variant == kCollideWg3 || variant == kCollideApart3) wg = 3;
+    else if (variant == kCollideWg4) wg = kMost;
+    else if (variant != kCollideWg2)
         while (wg < kMost && need <= collide_cap<VT, 64, VSS, ROT>(wg + 1, gmode)) ++wg;
     if constexpr (kMost == 4) {
         if (wg == 4) {

@@ -101,7 +101,7 @@ struct dsmc_ctx_s {
     // tuning choices
     int move_variant = dsmcx::kMoveFace3;
     int move_batch = 0;
-    int collide_variant = dsmcx::kCollideG3k;
+    int collide_variant = dsmcx::kCollideAuto;
     int sort_variant = dsmcx::kSortGather;
     int32_t* d_sortperm = nullptr;
     int reorder = 2;  // cell order: 0 caller's, 1 Morton, 2 Hilbert

@@ -433,7 +433,8 @@ __device__ __forceinline__ int link_cell(int link, int c) {
 // (67 lane by lane, the terms exchanged by shuffles), near the 160 B a cell
 // written and 40 read at the card's copy rate (15 us) and their latency.
 template <int NV>
-__global__ __launch_bounds__(kDigThreads) void k_dig_grad(DigGeom g, const double* prim, double* rec, const DigCtl* ctl) {
+__global__ __launch_bounds__(kDigThreads) void k_dig_grad(DigGeom g, const double* prim, double* rec,
+                                                          const DigCtl* ctl) {
     if (stopped(ctl)) return;
     constexpr int kT = 3 * NV;  // terms of a face
     constexpr int kR = 4 * NV;  // a record
@@ -779,7 +780,8 @@ __global__ __launch_bounds__(kDigThreads, NV == 6 ? 2 : 3) void k_dig_residual(D
     if constexpr (UPDATE) {
 #pragma unroll
         for (int k = 0; k < 2; ++k)
-            bs[k] = base[min((int64_t)NV * (c - (lane >> 2)) + min(lane + 64 * k, 16 * NV - 1), (int64_t)NV * g.nt - 1)];
+            bs[k] = base[min((int64_t)NV * (c - (lane >> 2)) + min(lane + 64 * k, 16 * NV - 1),
+                             (int64_t)NV * g.nt - 1)];
     }
     const int cw = blockIdx.x * (kDigThreads / 4) + lane;  // the first wave's cells
     if (threadIdx.x < 64 && cw < g.nt) {
@@ -1405,8 +1407,8 @@ void launch_dig_copy(hipStream_t s, const double* src, double* dst, int64_t n) {
 }
 
 template <bool UPDATE>
-void run_residual(hipStream_t s, const DigGeom& g, const DigWork& w, const double* hotf, double* Rs, bool first, double cfl,
-                  const double* base, double* out, double alpha) {
+void run_residual(hipStream_t s, const DigGeom& g, const DigWork& w, const double* hotf, double* Rs, bool first,
+                  double cfl, const double* base, double* out, double alpha) {
     const auto k = g.dr ? (first ? k_dig_residual<kDigNVR, UPDATE, true> : k_dig_residual<kDigNVR, UPDATE, false>)
                         : (first ? k_dig_residual<kDigNV, UPDATE, true> : k_dig_residual<kDigNV, UPDATE, false>);
     hipLaunchKernelGGL(k, cells_grid(4 * (int64_t)g.nt), dim3(kDigThreads), 0, s, g, (const double*)w.rec, hotf, Rs, w,
@@ -1633,7 +1635,8 @@ __device__ __forceinline__ void nk_block_dots(double (*red)[kDigThreads / 64], c
 }
 
 // Fixed-order sum over the blocks of column blockIdx.x into out[blockIdx.x].
-__global__ __launch_bounds__(kDigThreads) void k_nk_reduce(const DigCtl* ctl, const double* part, int nblk, double* out) {
+__global__ __launch_bounds__(kDigThreads) void k_nk_reduce(const DigCtl* ctl, const double* part, int nblk,
+                                                           double* out) {
     if (stopped(ctl)) return;
     const double* p = part + (size_t)blockIdx.x * nblk;
     double s = 0.0;
@@ -2043,8 +2046,8 @@ void launch_nk_begin(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, NkSc
 }
 
 void launch_nk_report(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk) {
-    hipLaunchKernelGGL(k_nk_started, dim3(1), dim3(kDigThreads), 0, s, nk, (const DigCtl*)w.ctl, (int)cells_grid(g.nt).x,
-                       nk.host);
+    hipLaunchKernelGGL(k_nk_started, dim3(1), dim3(kDigThreads), 0, s, nk, (const DigCtl*)w.ctl,
+                       (int)cells_grid(g.nt).x, nk.host);
 }
 
 void launch_nk_scale(hipStream_t s, const DigGeom& g, DigWork w, NkWork nk, double cfl, double fd) {

@@ -20,24 +20,25 @@ constexpr int kInflowStride = 25;       // doubles per inflow face
 enum { kScanPlain = 0, kScanCells = 1, kScanInject = 2, kScanInit = 3 };
 enum { kFlagCapacity = 1 };
 // move kernel variants (tuning choice)
-enum { kMoveLane = 0, kMoveLaneW6 = 1, kMoveLaneW8 = 2, kMoveBatched = 3, kMoveDefer6 = 4, kMoveDefer8 = 5, kMoveDefer4 = 6,
-       kMoveDefer5 = 7, kMoveRefill5 = 8, kMoveRefill6 = 9,
+enum { kMoveLane = 0, kMoveLaneW6 = 1, kMoveLaneW8 = 2, kMoveBatched = 3, kMoveDefer6 = 4, kMoveDefer8 = 5,
+       kMoveDefer4 = 6, kMoveDefer5 = 7, kMoveRefill5 = 8, kMoveRefill6 = 9,
        kMovePool128 = 10, kMovePool256 = 11, kMoveCap4 = 12, kMoveCap5 = 13, kMoveCap6 = 14,
        kMoveFace3 = 15, kMoveFace3W8 = 16, kMovePersist = 17 };
-// collide schedules: workgroups per CU (0 and 2: three, 1: two, 4: four, or
-// three where the stage would be too small; 3, the default: by occupancy and
-// mesh size).  All of them take 16-cell workgroups where the particles of 64
-// cells exceed the largest stage.
-enum { kCollideLds = 0, kCollideGlobal = 1, kCollideGlobal8 = 2, kCollideG3k = 3, kCollideG2k = 4 };
+// collide schedules: workgroups per CU (Apart3 and Wg3: three; Wg2: two; Wg4:
+// four, or three where the stage would be too small; Auto, the default: by
+// occupancy and mesh size).  Apart3 leaves the sort's gather to a kernel of its
+// own, the others do it (collide_fuses_gather).  All of them take 16-cell
+// workgroups where the particles of 64 cells exceed the largest stage.
+enum { kCollideApart3 = 0, kCollideWg2 = 1, kCollideWg3 = 2, kCollideAuto = 3, kCollideWg4 = 4 };
 // sort: scatter by rank; gather and fused (k_perm, then the collide kernel
 // gathers each chunk as it stages it: 11.52M particles, 1,330 us a step against
 // 1,521 with k_gather, 36,000 particles 107 against 113; k_gather where no
-// collide follows or its schedule is not a G-type one; fused is refused for a
-// rotating gas); deferred (k_perm only:
-// the collide kernel reaches the particles through the sorted order, and the
-// next step's move reads them in that order and writes them sorted, so no
-// pass of its own moves the particle store; three-face move and G-type
-// collide schedules)
+// collide follows or its schedule leaves the gather apart; two names of one
+// schedule, of which fused is refused for a rotating gas); deferred (k_perm
+// only: the collide kernel reaches the particles through the sorted order, and
+// the next step's move reads them in that order and writes them sorted, so no
+// pass of its own moves the particle store; three-face move and a collide
+// schedule that can do the gather)
 enum { kSortScatter = 0, kSortGather = 1, kSortFused = 2, kSortDeferred = 3 };
 // how the collide kernel reaches the sorted particles: in place, gathered
 // into the sorted buffer first (fused sort), or through the sorted order
@@ -177,8 +178,7 @@ void launch_scatter(hipStream_t s, PartDev<VT> src, PartDev<VT> dst, const Scala
                     const uint32_t* rank, int64_t bound, int64_t cap, int32_t* perm, int variant);
 // gmode kGatherFused: p's slots (cells included) are filled from src through
 // sortperm; kGatherIndirect: slot d of the sorted order is particle
-// sortperm[d] of p, with its cell in src.cell[d] (both G-type schedules only:
-// collide_fuses_gather).
+// sortperm[d] of p (both only with schedules that collide_fuses_gather).
 template <class VT>
 void launch_collide_sample(hipStream_t s, PartDev<VT> p, const int32_t* offsets, const CollideParams& cp,
                            const Scalars* sc, int32_t* perm, int do_collide, int do_sample, int variant, int gmode,

@@ -576,8 +576,8 @@ void launch_mlp_forward(hipStream_t s, const MlpDev& m, const float* x, int64_t 
     // rows: 25 us against 26, 8,192: 18 against 21)
     if (n > kMlpSmallRows) {
         const int64_t tiles = (n + 63) / 64;
-        hipLaunchKernelGGL(k_mlp_forward<4>, dim3((unsigned)(tiles < kMlpGrid ? tiles : kMlpGrid)), dim3(kThreads), 0, s,
-                           m, x, n, y);
+        hipLaunchKernelGGL(k_mlp_forward<4>, dim3((unsigned)(tiles < kMlpGrid ? tiles : kMlpGrid)), dim3(kThreads), 0,
+                           s, m, x, n, y);
     } else {
         hipLaunchKernelGGL(k_mlp_forward<2>, dim3((unsigned)((n + 31) / 32)), dim3(kThreads), 0, s, m, x, n, y);
     }
@@ -598,7 +598,8 @@ void launch_mlp_reduce(hipStream_t s, const float* partial, const float* loss_pa
 }
 
 MlpAdam mlp_adam(int step, float lr, float b1, float b2, float eps) {
-    return MlpAdam{lr, b1, b2, eps, (float)(1.0 - std::pow((double)b1, step)), (float)(1.0 - std::pow((double)b2, step))};
+    const auto c = [step](float b) { return (float)(1.0 - std::pow((double)b, step)); };
+    return MlpAdam{lr, b1, b2, eps, c(b1), c(b2)};
 }
 
 void launch_mlp_adam(hipStream_t s, float* params, const float* grad, float* m, float* v, const MlpAdam& a,
@@ -608,8 +609,8 @@ void launch_mlp_adam(hipStream_t s, float* params, const float* grad, float* m, 
 
 void launch_mlp_step(hipStream_t s, const float* partial, const float* loss_partial, int64_t nblk, double* loss,
                      float* params, float* m, float* v, const MlpAdam& a, uint16_t* packed) {
-    hipLaunchKernelGGL(k_mlp_step, dim3(kParamBlocks + 1), dim3(kReduceThreads), 0, s, partial, loss_partial, nblk, loss,
-                       params, m, v, a, packed);
+    hipLaunchKernelGGL(k_mlp_step, dim3(kParamBlocks + 1), dim3(kReduceThreads), 0, s, partial, loss_partial, nblk,
+                       loss, params, m, v, a, packed);
 }
 
 void launch_mlp_init(hipStream_t s, float* params, RngKey key) {

@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 KB = 1.380649e-23
 GASES = {"argon": W.Species(),
-         "nitrogen": W.Species(mass=4.65e-26, d_ref=4.17e-10, omega=0.74, T_ref=273.0, alpha=1.0, dof_rot=2, z_rot=2.59)}
+         "nitrogen": W.Species(mass=4.65e-26, d_ref=4.17e-10, omega=0.74, T_ref=273.0, alpha=1.0, dof_rot=2,
+                               z_rot=2.59)}
 
 
 @pytest.fixture(scope="module")

@@ -11,7 +11,8 @@ from oracle import Oracle
 pytestmark = pytest.mark.gpu
 
 GASES = {"argon": W.Species(),
-         "nitrogen": W.Species(mass=4.65e-26, d_ref=4.17e-10, omega=0.74, T_ref=273.0, alpha=1.0, dof_rot=2, z_rot=2.59)}
+         "nitrogen": W.Species(mass=4.65e-26, d_ref=4.17e-10, omega=0.74, T_ref=273.0, alpha=1.0, dof_rot=2,
+                               z_rot=2.59)}
 
 
 @pytest.fixture(scope="module")

@@ -12,8 +12,9 @@ namespace dsmcx {
 // ---------------------------------------------------------------------------
 // collisions and sampling
 // ---------------------------------------------------------------------------
-// A workgroup of four waves works on some consecutive cells (64, or 16 on a
-// small mesh) whose particles it stages in LDS (see k_collide_sample).
+// A workgroup of four waves (one where the cells are sparse) works on some
+// consecutive cells (64; 16 on a small mesh or of dense cells) whose particles
+// it stages in LDS (see k_collide_sample).
 
 // Velocities (and rotational energies) of a window of cells, staged in LDS
 // in slot order and written back as a whole (deferred sort: a changed value
@@ -74,7 +75,6 @@ struct Stored {
     __device__ __forceinline__ void putI(int l, double e) const { ir[l] = e; }
 };
 
-constexpr int kStageBatch = 8;  // particles per lane loaded together
 // Particles from which a cell's ids are ranked by all lanes of the workgroup
 // instead of the few that are the cell's.  These make a pass over the N ids per
 // 48 or 64 of them, the workgroup one per 1,024, but cell after cell, up to
@@ -104,18 +104,18 @@ __device__ __forceinline__ void rank4(uint32_t o, const uint32_t* p, int* r) {
 // What the candidate pairs of a round need besides the velocities: it
 // depends on the generator alone, so it is computed one candidate per lane,
 // the candidates of all the cells packed together.
-template <int CC, bool VSS, bool ROT, class H>
+template <int CC, int S, bool VSS, bool ROT, class H>
 struct PairSlots {
-    static constexpr int kCells = CC;
+    static constexpr int kCells = CC, kSlots = S;
     typedef H handle;
     // VHS: cos(theta), sin(theta) cos(eps), sin(theta) sin(eps); VSS:
     // cos(chi), sin(chi), cos(eps), sin(eps); then, rotating gas, the
     // translational shares of the two partners (-1: no exchange)
     static constexpr int kDir = VSS ? 4 : 3;
     static constexpr int kVals = kDir + (ROT ? 2 : 0);
-    double U[kPairSlots];
-    double val[kVals][kPairSlots];
-    H pi[kPairSlots], pj[kPairSlots];        // the partners
+    double U[S];
+    double val[kVals][S];
+    H pi[S], pj[S];                          // the partners
     int32_t first[CC];                       // first slot of each cell
     int32_t base[CC];                        // candidate index of slot 0, per cell
     int total;
@@ -328,7 +328,8 @@ __device__ __forceinline__ void ntc_round(const Acc& cv, const Slots& ps, int ba
 // The sums of a cell are shared out over the workgroup's waves, one lane per
 // cell in each: wave 0 takes S3, wave 1 the diagonal S2, wave 2 the
 // off-diagonal S2, wave 3 S1, the particle count S0 and (rotating gas) sum
-// I_r and sum v_i I_r.  Rows of the accumulators: g ... g + 2.
+// I_r and sum v_i I_r (a workgroup of one wave takes the four shares one after
+// another).  Rows of the accumulators: g ... g + 2.
 __device__ __forceinline__ int sum_rows(int wave) { return wave == 0 ? 10 : wave == 1 ? 4 : wave == 2 ? 7 : 1; }
 
 // Old values of the accumulators that this lane updates, requested ahead of
@@ -459,8 +460,8 @@ __device__ __forceinline__ void load_info(CellInfo& f, int c, const CollideParam
 
 // Collisions of the cells of a window (lane l of every wave: cell l, `live`
 // when it is one of them, its N particles in cv from s0), then their sums.
-// Candidate pairs are taken in rounds of at most kPairSlots: drawn one per
-// lane by all four waves, then decided and applied cell by cell, one cell per
+// Candidate pairs are taken in rounds of at most a lane each: drawn one per
+// lane by all waves, then decided and applied cell by cell, one cell per
 // lane, by wave 0.
 template <bool VSS, bool ROT, class Acc, class Slots, class Table>
 __device__ __forceinline__ void collide_cells(const Acc& cv, bool live, int s0, int N, int c, int wave, Slots& ps,
@@ -491,7 +492,7 @@ __device__ __forceinline__ void collide_cells(const Acc& cv, bool live, int s0, 
             int m = 0, base = 0;
             if (wave == 0) {
                 int total;
-                m = share_slots<kPairSlots>(left, &base, &total);
+                m = share_slots<Slots::kSlots>(left, &base, &total);
                 if (lane < Slots::kCells) {
                     ps.first[lane] = base;
                     ps.base[lane] = kb - base;
@@ -515,24 +516,34 @@ __device__ __forceinline__ void collide_cells(const Acc& cv, bool live, int s0, 
             cp.nacc[c] = acc;
         }
     }
-    if (do_sample && live) sample_cell<ROT>(cv, s0, N, c, wave, cp, (int64_t)step > (int64_t)cp.n_ss, sums);
+    const bool steady = (int64_t)step > (int64_t)cp.n_ss;
+    if constexpr (Slots::kSlots > 64) {
+        if (do_sample && live) sample_cell<ROT>(cv, s0, N, c, wave, cp, steady, sums);
+    } else if (do_sample && live) {
+        // one wave: the four shares of the sums one after another
+        CellSums<ROT> a[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) load_sums<ROT>(a[x], c, x, cp, steady);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) sample_cell<ROT>(cv, s0, N, c, x, cp, steady, a[x]);
+    }
 }
 
-// Particles that fit when `wg` workgroups share a CU's LDS: 128 units of
-// 1,280 bytes (gfx950 hands it out in these; a workgroup a few bytes over a
+// Particles that fit when `wg` workgroups of L lanes share a CU's LDS: 128 units
+// of 1,280 bytes (gfx950 hands it out in these; a workgroup a few bytes over a
 // third of it leaves room for two only).
-template <class VT, int CC, bool IND, bool VSS, bool ROT>
+template <class VT, int CC, int L, bool IND, bool VSS, bool ROT>
 constexpr int stage_cap(int wg) {
     // the ids share the candidate slots' memory, or have it to themselves
     // where they need more
-    const int slots = (int)sizeof(PairSlots<CC, VSS, ROT, uint16_t>);
+    const int slots = (int)sizeof(PairSlots<CC, L, VSS, ROT, uint16_t>);
     const int room = (128 / wg) * 1280 - (int)sizeof(CellTable<CC>) - 4 * (CC + 1) - 64;
     const int per = 3 * (int)sizeof(VT) + 2 + (IND ? 4 : 0) + (ROT ? 8 : 0);
     const int cap = (room - slots) / per;
     return (4 * cap <= slots ? cap : std::max(slots / 4, room / (per + 4))) & ~31;
 }
 
-// A workgroup works on CC consecutive cells.  Per window of them whose
+// A workgroup of L lanes works on CC consecutive cells.  Per window of them whose
 // particles fit the stage (one window as a rule) the particles' ids and
 // velocities (rotational energies) are staged in LDS with one round of
 // coalesced loads, and four lanes a cell (16 in workgroups of 16 cells, all of
@@ -555,20 +566,19 @@ constexpr int stage_cap(int wg) {
 // issue) takes 54 % of its time, those waits the rest.  One wave per 64 cells
 // that drew, decided and summed cell by cell, a lane each, at 47-63 % lane
 // efficiency and two waves per SIMD, took 360 us; nitrogen on 73,000 cells 133
-// against 209 us.  With one to three particles a cell on hundreds of thousands
-// of cells that wave was the faster one (384,000 cells of one, nitrogen: 101
-// against 142 us): a workgroup's chain of phases is then all there is, and
-// fewer of them fit a CU.
-template <class VT, int CC, int WG, int GM, bool VSS, bool ROT>
-__global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(WG))) void k_collide_sample(
+// against 209 us.
+// (For sparse cells there are workgroups of one wave here too: L = 64.)
+template <class VT, int CC, int L, int WG, int GM, bool VSS, bool ROT>
+__global__ __launch_bounds__(L) __attribute__((amdgpu_waves_per_eu(WG * L / 256))) void k_collide_sample(
     PartDev<VT> p, const int32_t* offsets, CollideParams cp, const Scalars* sc, int32_t* perm, int do_collide,
     int do_sample, PartDev<VT> src, const int32_t* sortperm) {
     constexpr bool FUSED = GM == kGatherFused;
     constexpr bool IND = GM == kGatherIndirect;
-    constexpr int CAP = stage_cap<VT, CC, IND, VSS, ROT>(WG);
+    constexpr int CAP = stage_cap<VT, CC, L, IND, VSS, ROT>(WG);
+    constexpr int kStageBatch = L == 64 ? 4 : 8;  // particles per lane loaded together
     // also the candidate slots of a cell beyond the stage, whose candidates
     // name particles by 32-bit index
-    typedef PairSlots<CC, VSS, ROT, int32_t> StoredSlots;
+    typedef PairSlots<CC, L, VSS, ROT, int32_t> StoredSlots;
     constexpr int kStage = std::max(3 * CAP, (int)(sizeof(StoredSlots) / sizeof(VT)) + 1);
     __shared__ __attribute__((aligned(16))) VT lv[kStage];
     __shared__ double li[ROT ? CAP : 1];
@@ -576,7 +586,7 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
     __shared__ uint32_t idx[IND ? CAP : 1];
     // the ids are read before the candidate slots are written
     __shared__ union {
-        PairSlots<CC, VSS, ROT, uint16_t> ps;
+        PairSlots<CC, L, VSS, ROT, uint16_t> ps;
         uint32_t ids[CAP];
     } u;
     __shared__ CellTable<CC> tab;
@@ -585,7 +595,7 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
     const int tid = threadIdx.x, lane = tid & 63;
     // the wave that takes part 0 below works while the others wait: not the
     // same SIMD's in each workgroup of a CU
-    const int wave = __builtin_amdgcn_readfirstlane(((tid >> 6) + (blockIdx.x >> 8)) & 3);
+    const int wave = L == 64 ? 0 : __builtin_amdgcn_readfirstlane(((tid >> 6) + (blockIdx.x >> 8)) & 3);
     // Workgroups go round-robin over the 8 XCDs: eight consecutive ones of an
     // XCD take eight consecutive pieces of the cells, so that its L2 holds the
     // source lines that neighbouring cells' gathers share (40^3 cavity: 1.52 GB
@@ -597,14 +607,14 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
     if (c0 >= cp.nt) return;
     const int c = c0 + lane;
     const int64_t a = offsets[c0];
-    if (tid <= CC) soff[tid] = offsets[min(c0 + tid, nt)] - (int32_t)a;
+    for (int i = tid; i <= CC; i += L) soff[i] = offsets[min(c0 + i, nt)] - (int32_t)a;
     const uint32_t step = sc->step;
     // requested ahead of their use after the ranking
     CellInfo f{};
     CellSums<ROT> sums{};
     if (lane < CC && c < nt) {
         if (wave == 0) load_info(f, c, cp);
-        if (do_sample) load_sums<ROT>(sums, c, wave, cp, (int64_t)step > (int64_t)cp.n_ss);
+        if (L > 64 && do_sample) load_sums<ROT>(sums, c, wave, cp, (int64_t)step > (int64_t)cp.n_ss);
     }
     __syncthreads();
 #pragma unroll 1
@@ -612,13 +622,15 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
         // the cells from k0 on that fit the stage together (lane l looks at
         // cell l; offsets do not fall, so the fitting ones are consecutive)
         const int w0 = soff[k0];
-        const int k1 = k0 + __popcll(__ballot(lane >= k0 && lane < CC && soff[min(lane, CC - 1) + 1] - w0 <= CAP));
+        const int lo = soff[min(lane, CC - 1)], hi = soff[min(lane, CC - 1) + 1];
+        const int k1 = k0 + __popcll(__ballot(lane >= k0 && lane < CC && hi - w0 <= CAP));
+        uint64_t large = __ballot(lane >= k0 && lane < k1 && hi - lo > kRankAll);
         const int64_t base = a + w0;
         if (k1 == k0) {
             // one cell beyond the stage: its order by comparison of all ids
             const int N = soff[k0 + 1] - w0;
             if (FUSED) {
-                for (int k = tid; k < N; k += kCollideLanes) {
+                for (int k = tid; k < N; k += L) {
                     const int64_t d = base + k, j = sortperm[d];
                     for (int q = 0; q < 3; ++q) {
                         p.pos[3 * d + q] = src.pos[3 * j + q];
@@ -630,7 +642,7 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
                 }
                 __syncthreads();
             }
-            for (int k = tid; k < N; k += kCollideLanes) {
+            for (int k = tid; k < N; k += L) {
                 const int32_t l = IND ? sortperm[base + k] : (int32_t)(base + k);
                 const uint32_t pk = p.pid[l];
                 int r = 0;
@@ -646,7 +658,7 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
             continue;
         }
         const int wn = soff[k1] - w0;
-        for (int i0 = tid; i0 < wn; i0 += kStageBatch * kCollideLanes) {
+        for (int i0 = tid; i0 < wn; i0 += kStageBatch * L) {
             // kStageBatch particles per lane in flight
             int64_t x[kStageBatch];
             uint32_t id[kStageBatch];
@@ -655,7 +667,7 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
 #pragma unroll
             for (int b = 0; b < kStageBatch; ++b) {
                 // past the window: its last particle again (no branch around a load)
-                x[b] = base + min(i0 + b * kCollideLanes, wn - 1);
+                x[b] = base + min(i0 + b * L, wn - 1);
                 if (IND || FUSED) x[b] = sortperm[x[b]];
             }
             const PartDev<VT>& from = FUSED ? src : p;
@@ -669,7 +681,7 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
             }
 #pragma unroll
             for (int b = 0; b < kStageBatch; ++b) {
-                const int i = i0 + b * kCollideLanes;
+                const int i = i0 + b * L;
                 if (i < wn) {
                     u.ids[i] = id[b];
                     lv[3 * i] = v[b][0];
@@ -686,14 +698,14 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
             // logical order: lane q of a cell's `lanes` ranks the ids q, q +
             // lanes, ..., `batch` of them against one pass over the cell
             auto rank = [&](int lc, int N, int q, auto lanes, auto batch) {
-                constexpr int L = decltype(lanes)::value, B = decltype(batch)::value;
+                constexpr int G = decltype(lanes)::value, B = decltype(batch)::value;
                 const int s0 = soff[lc] - w0;
-                for (int b0 = q; b0 < N; b0 += L * B) {
+                for (int b0 = q; b0 < N; b0 += G * B) {
                     uint32_t pk[B];
                     int r[B];
 #pragma unroll
                     for (int t = 0; t < B; ++t) {
-                        const int x = b0 + L * t;
+                        const int x = b0 + G * t;
                         pk[t] = x < N ? u.ids[s0 + x] : 0u;
                         r[t] = s0;
                     }
@@ -705,7 +717,7 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
                     }
 #pragma unroll
                     for (int t = 0; t < B; ++t) {
-                        const int x = b0 + L * t;
+                        const int x = b0 + G * t;
                         if (x < N) {
                             ord[r[t]] = (uint16_t)(3 * (s0 + x));
                             if (FUSED) p.cell[base + s0 + x] = c0 + lc;
@@ -713,16 +725,15 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
                     }
                 }
             };
-            constexpr int kLanes = kCollideLanes / CC, kBatch = kLanes == 4 ? 12 : kLanes == 8 ? 8 : 4;
+            constexpr int kLanes = L / CC, kBatch = kLanes <= 4 ? 12 : kLanes == 8 ? 8 : 4;
             const int lc = tid / kLanes;
             const int N = lc >= k0 && lc < k1 ? soff[lc + 1] - soff[lc] : 0;
             rank(lc, N <= kRankAll ? N : 0, tid & (kLanes - 1), std::integral_constant<int, kLanes>{},
                  std::integral_constant<int, kBatch>{});
             // the large cells by all lanes, one after another
-            const int n = lane >= k0 && lane < k1 ? soff[min(lane, CC - 1) + 1] - soff[min(lane, CC - 1)] : 0;
-            for (uint64_t big = __ballot(n > kRankAll); big; big &= big - 1) {
-                const int k = __builtin_ctzll(big);
-                rank(k, soff[k + 1] - soff[k], tid, std::integral_constant<int, kCollideLanes>{},
+            for (; large; large &= large - 1) {
+                const int k = __builtin_ctzll(large);
+                rank(k, soff[k + 1] - soff[k], tid, std::integral_constant<int, L>{},
                      std::integral_constant<int, 4>{});
             }
         }
@@ -735,24 +746,24 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
         if (FUSED || (!IND && do_collide)) {
             // whole lines: written where they changed, 12 bytes here and
             // there, the same velocities took the memory several times as long
-            for (int i = tid; i < 3 * wn; i += kCollideLanes) p.vel[3 * base + i] = lv[i];
+            for (int i = tid; i < 3 * wn; i += L) p.vel[3 * base + i] = lv[i];
             if (ROT)
-                for (int i = tid; i < wn; i += kCollideLanes) p.ir[base + i] = li[i];
+                for (int i = tid; i < wn; i += L) p.ir[base + i] = li[i];
         }
         if (FUSED) {
             // positions only pass through (next read by the following step's move)
-            for (int i0 = tid; i0 < wn; i0 += kStageBatch * kCollideLanes) {
+            for (int i0 = tid; i0 < wn; i0 += kStageBatch * L) {
                 double x[kStageBatch][3];
 #pragma unroll
                 for (int b = 0; b < kStageBatch; ++b) {
-                    const int64_t j = sortperm[base + min(i0 + b * kCollideLanes, wn - 1)];
+                    const int64_t j = sortperm[base + min(i0 + b * L, wn - 1)];
                     x[b][0] = src.pos[3 * j];
                     x[b][1] = src.pos[3 * j + 1];
                     x[b][2] = src.pos[3 * j + 2];
                 }
 #pragma unroll
                 for (int b = 0; b < kStageBatch; ++b) {
-                    const int i = i0 + b * kCollideLanes;
+                    const int i = i0 + b * L;
                     if (i < wn) {
                         double* d = p.pos + 3 * (base + i);
                         __builtin_nontemporal_store(x[b][0], d);
@@ -768,30 +779,30 @@ __global__ __launch_bounds__(kCollideLanes) __attribute__((amdgpu_waves_per_eu(W
 }
 
 // Particles that the instance with wg workgroups per CU stages at once.
-template <class VT, int CC, bool VSS, bool ROT>
+template <class VT, int CC, int L, bool VSS, bool ROT>
 static int collide_cap(int wg, int gmode) {
-    return gmode == kGatherIndirect ? stage_cap<VT, CC, true, VSS, ROT>(wg)
-                                    : stage_cap<VT, CC, false, VSS, ROT>(wg);
+    return gmode == kGatherIndirect ? stage_cap<VT, CC, L, true, VSS, ROT>(wg)
+                                    : stage_cap<VT, CC, L, false, VSS, ROT>(wg);
 }
 
 bool collide_fuses_gather(int variant) { return variant != kCollideApart3; }
 
-template <class VT, int CC, int WG, bool VSS, bool ROT>
+template <class VT, int CC, int L, int WG, bool VSS, bool ROT>
 static void launch_collide_g(hipStream_t s, PartDev<VT> p, const int32_t* offsets, const CollideParams& cp,
                              const Scalars* sc, int32_t* perm, int do_collide, int do_sample, int gmode,
                              PartDev<VT> src, const int32_t* sortperm) {
-    const dim3 gr(((cp.nt + CC - 1) / CC + 63) / 64 * 64), bl(kCollideLanes);
+    const dim3 gr(((cp.nt + CC - 1) / CC + 63) / 64 * 64), bl(L);
     if (gmode == kGatherIndirect) {
-        hipLaunchKernelGGL((k_collide_sample<VT, CC, WG, kGatherIndirect, VSS, ROT>), gr, bl, 0, s, p, offsets, cp,
+        hipLaunchKernelGGL((k_collide_sample<VT, CC, L, WG, kGatherIndirect, VSS, ROT>), gr, bl, 0, s, p, offsets, cp,
                            sc, perm, do_collide, do_sample, src, sortperm);
         return;
     }
     if (gmode == kGatherFused) {
-        hipLaunchKernelGGL((k_collide_sample<VT, CC, WG, kGatherFused, VSS, ROT>), gr, bl, 0, s, p, offsets, cp, sc,
+        hipLaunchKernelGGL((k_collide_sample<VT, CC, L, WG, kGatherFused, VSS, ROT>), gr, bl, 0, s, p, offsets, cp, sc,
                            perm, do_collide, do_sample, src, sortperm);
         return;
     }
-    hipLaunchKernelGGL((k_collide_sample<VT, CC, WG, kGatherNone, VSS, ROT>), gr, bl, 0, s, p, offsets, cp, sc, perm,
+    hipLaunchKernelGGL((k_collide_sample<VT, CC, L, WG, kGatherNone, VSS, ROT>), gr, bl, 0, s, p, offsets, cp, sc, perm,
                        do_collide, do_sample, src, sortperm);
 }
 
@@ -811,8 +822,23 @@ static void launch_collide_v(hipStream_t s, PartDev<VT> p, const int32_t* offset
     // cell 0.49 against 0.63 ms, 450 5.2 against 10.3; FP64 450 7.4 against
     // 16.9; 83,000 cells of 90 0.97 against 1.09; of 60, which fit, 0.68
     // against 0.62).
-    if ((variant == kCollideAuto && cp.nt <= 64 * 512) || need > collide_cap<VT, 64, VSS, ROT>(2, gmode)) {
-        launch_collide_g<VT, 16, 3, VSS, ROT>(s, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src, sortperm);
+    if ((variant == kCollideAuto && cp.nt <= 64 * 512) || need > collide_cap<VT, 64, 256, VSS, ROT>(2, gmode)) {
+        launch_collide_g<VT, 16, 256, 3, VSS, ROT>(s, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src,
+                                                   sortperm);
+        return;
+    }
+    // Few particles a cell on many cells: the phases of a workgroup are a serial
+    // chain whatever it holds, and eight one-wave workgroups a CU have more of
+    // them under way than three or four of four waves (384,000 cells, us a step,
+    // FP32 / FP64 / FP64 nitrogen: one particle a cell 143 / 145 / 159 against
+    // 175 / 182 / 274, six 356 / 374 against 387 / 396 and nitrogen beyond the
+    // stage; 83,000 cells of six 122 / 124 against 124 / 126, of nine 146 / 147
+    // against 143 / 145; 35,000 cells of four 82 against 76).  Twelve a CU have
+    // registers spilled (216 for the nitrogen).
+    if (variant == kCollideAuto && cp.nt >= 64 * 1024 && np <= 6 * (int64_t)cp.nt &&
+        need <= collide_cap<VT, 64, 64, VSS, ROT>(8, gmode)) {
+        launch_collide_g<VT, 64, 64, 8, VSS, ROT>(s, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src,
+                                                  sortperm);
         return;
     }
     // Workgroups per CU: the most for which the stage holds a workgroup's
@@ -829,18 +855,20 @@ static void launch_collide_v(hipStream_t s, PartDev<VT> p, const int32_t* offset
     if (variant == kCollideWg3 || variant == kCollideApart3) wg = 3;
     else if (variant == kCollideWg4) wg = kMost;
     else if (variant != kCollideWg2)
-        while (wg < kMost && need <= collide_cap<VT, 64, VSS, ROT>(wg + 1, gmode)) ++wg;
+        while (wg < kMost && need <= collide_cap<VT, 64, 256, VSS, ROT>(wg + 1, gmode)) ++wg;
     if constexpr (kMost == 4) {
         if (wg == 4) {
-            launch_collide_g<VT, 64, 4, VSS, ROT>(s, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src,
+            launch_collide_g<VT, 64, 256, 4, VSS, ROT>(s, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src,
                                                   sortperm);
             return;
         }
     }
     if (wg == 3)
-        launch_collide_g<VT, 64, 3, VSS, ROT>(s, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src, sortperm);
+        launch_collide_g<VT, 64, 256, 3, VSS, ROT>(s, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src,
+                                                   sortperm);
     else
-        launch_collide_g<VT, 64, 2, VSS, ROT>(s, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src, sortperm);
+        launch_collide_g<VT, 64, 256, 2, VSS, ROT>(s, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src,
+                                                   sortperm);
 }
 
 template <class VT>

@@ -14,8 +14,6 @@ constexpr int kScanItems = 16;
 constexpr int kScanBlock = kScanThreads * kScanItems;
 constexpr int kScanTopBlocks = 128;    // more blocks: their sums are scanned by a kernel of its own
 constexpr int kMoveBatch = 512;        // particles per wave in the move kernel
-constexpr int kCollideLanes = 256;      // four waves
-constexpr int kPairSlots = kCollideLanes;  // candidate pairs drawn at once
 constexpr int kInflowStride = 25;       // doubles per inflow face
 enum { kScanPlain = 0, kScanCells = 1, kScanInject = 2, kScanInit = 3 };
 enum { kFlagCapacity = 1 };
@@ -26,9 +24,10 @@ enum { kMoveLane = 0, kMoveLaneW6 = 1, kMoveLaneW8 = 2, kMoveBatched = 3, kMoveD
        kMoveFace3 = 15, kMoveFace3W8 = 16, kMovePersist = 17 };
 // collide schedules: workgroups per CU (Apart3 and Wg3: three; Wg2: two; Wg4:
 // four, or three where the stage would be too small; Auto, the default: by
-// occupancy and mesh size).  Apart3 leaves the sort's gather to a kernel of its
-// own, the others do it (collide_fuses_gather).  All of them take 16-cell
-// workgroups where the particles of 64 cells exceed the largest stage.
+// occupancy and mesh size, with workgroups of one wave for sparse cells on
+// many).  Apart3 leaves the sort's gather to a kernel of its own, the others do
+// it (collide_fuses_gather).  All of them take 16-cell workgroups where the
+// particles of 64 cells exceed the largest stage.
 enum { kCollideApart3 = 0, kCollideWg2 = 1, kCollideWg3 = 2, kCollideAuto = 3, kCollideWg4 = 4 };
 // sort: scatter by rank; gather and fused (k_perm, then the collide kernel
 // gathers each chunk as it stages it: 11.52M particles, 1,330 us a step against

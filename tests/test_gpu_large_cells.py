@@ -51,6 +51,10 @@ def _matches_oracle(D, wl, counts, sort, steps):
     assert np.array_equal(gc, oc) and np.array_equal(ga, oa)
     compare_particles(g.state(), o.particles(), vel_fp32)
     compare_sums(g.sums(D.SAMPLE_STEADY)[0], o.sums(0))
+    if wl.run.ewma_on:
+        compare_sums(g.sums(D.SAMPLE_EWMA)[0], o.sums(1))
+    if ir is not None:
+        compare_sums(g.rot_sums(D.SAMPLE_STEADY)[0], o.rot_sums(0))
     g.close()
 
 

@@ -210,7 +210,7 @@ dsmc_status run_step_deferred(dsmc_ctx c, bool inj, bool col, bool smp, int64_t 
         Timed t(c, kSlotCollide);
         const CollideParams cp = collide_params(c);
         launch_collide_sample<VT>(s, a, c->d_offsets, cp, c->d_sc, c->d_perm, col ? 1 : 0, smp ? 1 : 0,
-                                  c->collide_variant, kGatherIndirect, b, c->d_sortperm, c->np_seen);
+                                  c->collide_variant, kGatherIndirect, b, c->d_sortperm, c->np_seen, need);
     }
     c->pending = true;
     hipError_t e = hipGetLastError();
@@ -292,7 +292,7 @@ dsmc_status run_step(dsmc_ctx c, int mask) {
         const CollideParams cp = collide_params(c);
         launch_collide_sample<VT>(s, a, c->d_offsets, cp, c->d_sc, c->d_perm, col ? 1 : 0, smp ? 1 : 0,
                                   c->collide_variant, fuse ? kGatherFused : kGatherNone,
-                                  fuse ? as_dev<VT>(c->B) : PartDev<VT>{}, c->d_sortperm, c->np_seen);
+                                  fuse ? as_dev<VT>(c->B) : PartDev<VT>{}, c->d_sortperm, c->np_seen, need);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {

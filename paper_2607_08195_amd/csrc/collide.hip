@@ -809,7 +809,7 @@ static void launch_collide_g(hipStream_t s, PartDev<VT> p, const int32_t* offset
 template <class VT, bool VSS, bool ROT>
 static void launch_collide_v(hipStream_t s, PartDev<VT> p, const int32_t* offsets, const CollideParams& cp,
                              const Scalars* sc, int32_t* perm, int do_collide, int do_sample, int variant, int gmode,
-                             PartDev<VT> src, const int32_t* sortperm, int64_t np) {
+                             PartDev<VT> src, const int32_t* sortperm, int64_t np, int64_t bound) {
     const int64_t need = np * 64 * 12 / (11 * (int64_t)std::max(cp.nt, 1));
     // Cells per workgroup: 64, a lane of the deciding wave each, keep that
     // wave full; where they would give the device's 256 CUs fewer than two
@@ -835,8 +835,10 @@ static void launch_collide_v(hipStream_t s, PartDev<VT> p, const int32_t* offset
     // stage; 83,000 cells of six 122 / 124 against 124 / 126, of nine 146 / 147
     // against 143 / 145; 35,000 cells of four 82 against 76).  Twelve a CU have
     // registers spilled (216 for the nitrogen).
-    if (variant == kCollideAuto && cp.nt >= 64 * 1024 && np <= 6 * (int64_t)cp.nt &&
-        need <= collide_cap<VT, 64, 64, VSS, ROT>(8, gmode)) {
+    // The particles are counted by their upper bound: an inflow can fill the mesh
+    // before the count is next seen, or in replays of a graph captured now.
+    if (variant == kCollideAuto && cp.nt >= 64 * 1024 && bound <= 6 * (int64_t)cp.nt &&
+        bound * 64 * 12 / (11 * (int64_t)cp.nt) <= collide_cap<VT, 64, 64, VSS, ROT>(8, gmode)) {
         launch_collide_g<VT, 64, 64, 8, VSS, ROT>(s, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src,
                                                   sortperm);
         return;
@@ -874,27 +876,27 @@ static void launch_collide_v(hipStream_t s, PartDev<VT> p, const int32_t* offset
 template <class VT>
 void launch_collide_sample(hipStream_t s, PartDev<VT> p, const int32_t* offsets, const CollideParams& cp,
                            const Scalars* sc, int32_t* perm, int do_collide, int do_sample, int variant, int gmode,
-                           PartDev<VT> src, const int32_t* sortperm, int64_t np) {
+                           PartDev<VT> src, const int32_t* sortperm, int64_t np, int64_t bound) {
     if (cp.rot) {
         if (cp.vss)
             launch_collide_v<VT, true, true>(s, p, offsets, cp, sc, perm, do_collide, do_sample, variant, gmode, src,
-                                             sortperm, np);
+                                             sortperm, np, bound);
         else
             launch_collide_v<VT, false, true>(s, p, offsets, cp, sc, perm, do_collide, do_sample, variant, gmode, src,
-                                              sortperm, np);
+                                              sortperm, np, bound);
     } else if (cp.vss) {
         launch_collide_v<VT, true, false>(s, p, offsets, cp, sc, perm, do_collide, do_sample, variant, gmode, src,
-                                          sortperm, np);
+                                          sortperm, np, bound);
     } else {
         launch_collide_v<VT, false, false>(s, p, offsets, cp, sc, perm, do_collide, do_sample, variant, gmode, src,
-                                           sortperm, np);
+                                           sortperm, np, bound);
     }
 }
 
 #define INSTANTIATE(VT)                                                                                      \
     template void launch_collide_sample<VT>(hipStream_t, PartDev<VT>, const int32_t*, const CollideParams&, \
                                             const Scalars*, int32_t*, int, int, int, int, PartDev<VT>,      \
-                                            const int32_t*, int64_t);
+                                            const int32_t*, int64_t, int64_t);
 
 INSTANTIATE(float)
 INSTANTIATE(double)

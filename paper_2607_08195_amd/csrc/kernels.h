@@ -177,11 +177,12 @@ void launch_scatter(hipStream_t s, PartDev<VT> src, PartDev<VT> dst, const Scala
                     const uint32_t* rank, int64_t bound, int64_t cap, int32_t* perm, int variant);
 // gmode kGatherFused: p's slots (cells included) are filled from src through
 // sortperm; kGatherIndirect: slot d of the sorted order is particle
-// sortperm[d] of p (both only with schedules that collide_fuses_gather).
+// sortperm[d] of p (both only with schedules that collide_fuses_gather).  np:
+// particles when last counted, bound: at most; they choose the kernel's instance.
 template <class VT>
 void launch_collide_sample(hipStream_t s, PartDev<VT> p, const int32_t* offsets, const CollideParams& cp,
                            const Scalars* sc, int32_t* perm, int do_collide, int do_sample, int variant, int gmode,
-                           PartDev<VT> src, const int32_t* sortperm, int64_t np);
+                           PartDev<VT> src, const int32_t* sortperm, int64_t np, int64_t bound);
 bool collide_fuses_gather(int variant);
 void launch_fields(hipStream_t s, const double* sums, int nt, double ns, double mass, double FN,
                    const double* vol, const int32_t* orig, double* out, const int32_t* cell_case,

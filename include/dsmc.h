@@ -417,9 +417,10 @@ dsmc_status dsmc_graph_step(dsmc_ctx ctx, int32_t n_steps);
  * collide (one kernel, particles staged in LDS) 1/2/4 with two, three and
  * up to four workgroups per CU (the fewer, the more particles each stages
  * at once), 3 (default) chosen by the mean particles per cell and the mesh
- * size (workgroups of one wave for sparse cells on many), 0 as 2 but refused for a rotating gas and the deferred sort (where the
- * particles of 64 cells exceed the largest stage, all of them use workgroups of
- * 16 cells, three per CU);
+ * size (workgroups of one wave for sparse cells on many), 0 as 2 but refused
+ * for a rotating gas and the deferred sort (where the particles of 64 cells
+ * exceed three of the largest stage, all of them use workgroups of 16 cells,
+ * three per CU);
  * sort 0 scatter, 1 (default) gather, done by the collide kernel chunk by chunk
  * (by a kernel of its own with collide 0 or where no collide follows), 2 as 1
  * but refused for a rotating gas, 3 deferred.  The autotuner's collide_ms

@@ -816,13 +816,14 @@ static void launch_collide_v(hipStream_t s, PartDev<VT> p, const int32_t* offset
     // workgroups each, 16 (1,296 cells, FP64: 20.0 against 24.5 us; 24,500
     // cells, VSS: 104 against 130 us; but 73,000 cells of nitrogen 194
     // against 133 us, 384,000 of argon 707 against 281 us).  Also 16 where 64
-    // cells' particles exceed even the largest stage: in windows of a few
+    // cells' particles exceed even three of the largest stage: in windows of a few
     // cells most lanes of the deciding waves idle, and three of these waves a
-    // CU decide more than two (35,000 cells, FP32, a step: 100 particles a
-    // cell 0.49 against 0.63 ms, 450 5.2 against 10.3; FP64 450 7.4 against
-    // 16.9; 83,000 cells of 90 0.97 against 1.09; of 60, which fit, 0.68
-    // against 0.62).
-    if ((variant == kCollideAuto && cp.nt <= 64 * 512) || need > collide_cap<VT, 64, 256, VSS, ROT>(2, gmode)) {
+    // CU decide more than two (35,000 cells, a step: FP32 250 particles a cell
+    // 1.77 against 2.70 ms, 450 5.2 against 10.3; FP64 450 7.4 against 16.9;
+    // 162,000 cells, FP64, 125 a cell 3.49 against 3.84).  Below, some meshes
+    // gain and some lose (nitrogen, FP64: 162,000 cells of 80 2.47 against 2.33;
+    // 83,000 of 15 and 165 at random, without the move, 1.72 against 1.53).
+    if ((variant == kCollideAuto && cp.nt <= 64 * 512) || need > 3 * collide_cap<VT, 64, 256, VSS, ROT>(2, gmode)) {
         launch_collide_g<VT, 16, 256, 3, VSS, ROT>(s, p, offsets, cp, sc, perm, do_collide, do_sample, gmode, src,
                                                    sortperm);
         return;

@@ -27,7 +27,7 @@ enum { kMoveLane = 0, kMoveLaneW6 = 1, kMoveLaneW8 = 2, kMoveBatched = 3, kMoveD
 // occupancy and mesh size, with workgroups of one wave for sparse cells on
 // many).  Apart3 leaves the sort's gather to a kernel of its own, the others do
 // it (collide_fuses_gather).  All of them take 16-cell workgroups where the
-// particles of 64 cells exceed the largest stage.
+// particles of 64 cells exceed three of the largest stage.
 enum { kCollideApart3 = 0, kCollideWg2 = 1, kCollideWg3 = 2, kCollideAuto = 3, kCollideWg4 = 4 };
 // sort: scatter by rank; gather and fused (k_perm, then the collide kernel
 // gathers each chunk as it stages it: 11.52M particles, 1,330 us a step against
